@@ -201,7 +201,11 @@ int build_passes(const Geometry &g, int dtype, int dir, int flags, std::vector<P
             p.nlines = p.es;
             p.nw = N / (p.es * n);
         }
-        int cand = 0, waves = 1;
+        // no measured choice: candidate 0, one block per tile (0.8 GB moved,
+        // complex64, against one wave of resident blocks looping over the
+        // tiles: strided 25 132 us against 159, 150 149 against 160, 300
+        // contiguous 141 against 164; below 24 MB level)
+        int cand = 0, waves = 0;
         wisdom_lookup(n, p.kind, dtype, dir, wisdom_axis(p.kind, axis), &cand, &waves);
         if (!select_kernel(n, p.kind, dtype, (flags & CROFT_FORCE_GENERIC) != 0, cand, &p.cfg))
             return no_kernel(n, dtype);
@@ -268,7 +272,7 @@ int build_unfused_passes(const Geometry &g, int dtype, int dir, int flags, std::
         p.es = 1;
         p.nlines = N / p.n;
         p.nw = 1;
-        int cand = 0, waves = 1;
+        int cand = 0, waves = 0;
         wisdom_lookup(p.n, kContiguous, dtype, dir, -1, &cand, &waves);
         const bool generic = (flags & CROFT_FORCE_GENERIC) != 0 || p.n == 1;
         if (!select_kernel(p.n, kContiguous, dtype, generic, cand, &p.cfg)) return no_kernel(p.n, dtype);
@@ -314,6 +318,7 @@ int build_real_passes(const Geometry &g, int dtype, int dir, int flags, std::vec
         p.es = axis == 1 ? h : h * g.ny;
         p.nlines = p.es;
         p.nw = axis == 1 ? g.nz : 1;
+        cand = waves = 0;
         wisdom_lookup(n, kStrided, dtype, tune_dir, axis, &cand, &waves);
         if (!select_kernel(n, kStrided, dtype, (flags & CROFT_FORCE_GENERIC) != 0, cand, &p.cfg))
             return no_kernel(n, dtype);
@@ -696,6 +701,7 @@ int measure_passes(croft_plan *p) {
                 // (e.g. one spills registers), so both are timed
                 const int ndir = cfg.func_inv != cfg.func ? 2 : 1;
                 for (int waves : {1, 2, 4, 0}) {
+                    if (cfg.one_tile && waves != 0) continue;
                     float total = 0.f;
                     for (const PassLaunch *q : same) {
                         PassLaunch t = *q;

@@ -1739,6 +1739,7 @@ struct Entry {
     RPlan plan;
     int plain = -1;  // non-temporal candidates: the candidate without the hint
     bool whole_tiles = false;  // runs only where every tile is whole (es a multiple of L)
+    bool one_tile = false;     // the kernel does not loop: one block per tile always
 };
 
 // An entry whose kernel uses the non-temporal hint, with the candidate index

@@ -10,6 +10,9 @@ namespace dev {
 
 #define DEF(N) make_entry<N, kContiguous, StC128, 16, kC128>(0), make_entry<N, kStrided, StC128, 16, kC128>(0), make_real_entry<N, StC128, 16, kC128>(), \
                make_conv_entry<N, StC128, 16, kC128>(0)
+// lengths whose strided pass is in croft_group_c128.hip
+#define DEFX(N) make_entry<N, kContiguous, StC128, 16, kC128>(0), make_real_entry<N, StC128, 16, kC128>(), \
+                make_conv_entry<N, StC128, 16, kC128>(0)
 // contiguous: 1 padded LDS lines, 2 no prefetch;
 // strided: 1 no prefetch, 2 wide tile (EW elements per thread, LW lines), 3 wide tile with prefetch,
 // 4 wide tile with fewer threads (EW2 elements per thread, LW2 lines),
@@ -28,22 +31,16 @@ namespace dev {
         make_entry<N, kStrided, StC128, 16, kC128, EW, LW, 0, 0, 1>(5), \
         make_conv_entry<N, StC128, 16, kC128, EW, LW>(1)
 
-// the larger compiled 2^a 3^b 5^c lengths: the streaming contiguous tile, the
-// strided tile without prefetch, and both strided tiles in the XCD-contiguous
-// order (numbered as the complex64 ones)
-#define XCAND(N)                                                                   \
-    make_entry<N, kContiguous, StC128, 16, kC128, 0, 0, 0, 1, 1>(3),               \
-        make_entry<N, kStrided, StC128, 16, kC128, 0, 0, 0, 0>(1),                 \
-        make_entry<N, kStrided, StC128, 16, kC128, 0, 0, 0, 0, 0, 1>(6),           \
-        make_entry<N, kStrided, StC128, 16, kC128, 0, 0, 0, 1, 0, 1>(7)
+// the larger compiled 2^a 3^b 5^c lengths: the streaming contiguous tile
+#define XCAND(N) make_entry<N, kContiguous, StC128, 16, kC128, 0, 0, 0, 1, 1>(3)
 
 std::vector<Entry> entries_c128() {
     return {
         DEF(2),   DEF(4),   DEF(8),   DEF(16),   DEF(32),   DEF(64),   DEF(128),
         DEF(256), DEF(512), DEF(1024), DEF(2048), DEF(4096), DEF(48),  DEF(60),
-        DEF(72),  DEF(80),  DEF(96),  DEF(100), DEF(384), DEF(120), DEF(160),
-        DEF(192), DEF(240), DEF(320), DEF(480), DEF(200), DEF(288), DEF(360),
-        DEF(400), DEF(576), DEF(640), DEF(720), DEF(768), DEF(960),
+        DEF(72),  DEF(80),  DEF(96),  DEF(100), DEFX(384), DEF(120), DEF(160),
+        DEF(192), DEF(240), DEFX(320), DEFX(480), DEF(200), DEFX(288), DEFX(360),
+        DEFX(400), DEFX(576), DEFX(640), DEFX(720), DEFX(768), DEFX(960),
         CAND(128, 8, 16, 16, 16), CAND(256, 8, 16, 16, 16), CAND(512, 8, 16, 16, 16), CAND(1024, 16, 8, 32, 8),
         make_entry<512, kStrided, StC128, 16, kC128, 0, 0, 0, 0, 0, 1>(6),
         make_entry<512, kStrided, StC128, 16, kC128, 8, 16, 0, 0, 0, 1>(7),

@@ -10,6 +10,9 @@ namespace dev {
 
 #define DEF(N) make_entry<N, kContiguous, StC64, 8, kC64>(0), make_entry<N, kStrided, StC64, 8, kC64>(0), make_real_entry<N, StC64, 8, kC64>(), \
                make_conv_entry<N, StC64, 8, kC64>(0)
+// lengths whose strided pass (DEFX) and contiguous pass too (DEFR) are in croft_group_c64.hip
+#define DEFR(N) make_real_entry<N, StC64, 8, kC64>(), make_conv_entry<N, StC64, 8, kC64>(0)
+#define DEFX(N) make_entry<N, kContiguous, StC64, 8, kC64>(0), DEFR(N)
 // contiguous: 1 padded LDS lines, 2 no prefetch;
 // strided: 1 no prefetch, 2 wide tile (EW elements per thread, LW lines), 3 wide tile with prefetch,
 // 4 wide tile with fewer threads (EW2 elements per thread, LW2 lines),
@@ -25,7 +28,7 @@ namespace dev {
 // in 12); contiguous 3:
 // non-temporal;
 // fused multiply pass: 0 default shape, 1 wide tile (EW, LW); strided 384: 6 and 7 are 1 and 0
-// (without and with prefetch) in the XCD-contiguous tile order
+// (without and with prefetch) in the XCD-contiguous tile order, 8 is in croft_group_c64.hip
 #define CAND(N, EW, LW, EW2, LW2)                                                \
     make_entry<N, kContiguous, StC64, 8, kC64, 0, 0, 1, 1>(1),                 \
         make_entry<N, kContiguous, StC64, 8, kC64, 0, 0, 0, 0>(2),             \
@@ -37,22 +40,13 @@ namespace dev {
         make_entry<N, kStrided, StC64, 8, kC64, EW, LW, 0, 0, 1>(5), \
         make_conv_entry<N, StC64, 8, kC64, EW, LW>(1)
 
-// the larger compiled 2^a 3^b 5^c lengths (16-line strided tiles): the
-// streaming contiguous tile, the strided tile without prefetch, and both
-// strided tiles in the XCD-contiguous order (numbered as at 384)
-#define XCAND(N)                                                                  \
-    make_entry<N, kContiguous, StC64, 8, kC64, 0, 0, 0, 1, 1>(3),                 \
-        make_entry<N, kStrided, StC64, 8, kC64, 0, 0, 0, 0>(1),                   \
-        make_entry<N, kStrided, StC64, 8, kC64, 0, 0, 0, 0, 0, 1>(6),             \
-        make_entry<N, kStrided, StC64, 8, kC64, 0, 0, 0, 1, 0, 1>(7)
-
 std::vector<Entry> entries_c64() {
     return {
         DEF(2),   DEF(4),   DEF(8),   DEF(16),   DEF(32),   DEF(64),   DEF(128),
         DEF(256), DEF(512), DEF(1024), DEF(2048), DEF(4096), DEF(48),  DEF(60),
         DEF(72),  DEF(80),  DEF(96),  DEF(100), DEF(384), DEF(120), DEF(160),
-        DEF(192), DEF(240), DEF(320), DEF(480), DEF(200), DEF(288), DEF(360),
-        DEF(400), DEF(576), DEF(640), DEF(720), DEF(768), DEF(960),
+        DEF(192), DEF(240), DEFX(320), DEFX(480), DEF(200), DEFX(288), DEFX(360),
+        DEFX(400), DEFR(576), DEFR(640), DEFR(720), DEFR(768), DEFR(960),
         CAND(128, 16, 32, 32, 32), CAND(256, 16, 32, 32, 32), CAND(512, 16, 32, 32, 32), CAND(1024, 32, 16, 64, 16),
         make_lanes_entry<512, StC64, kC64, 0>(6), with_plain(make_lanes_entry<512, StC64, kC64, 3>(7), 6),
         make_lanes_entry<512, StC64, kC64, 0, 256>(8), with_plain(make_lanes_entry<512, StC64, kC64, 3, 256>(9), 8),
@@ -73,7 +67,7 @@ std::vector<Entry> entries_c64() {
         CAND(384, 16, 32, 32, 32),
         make_entry<384, kStrided, StC64, 8, kC64, 0, 0, 0, 0, 0, 1>(6),
         make_entry<384, kStrided, StC64, 8, kC64, 0, 0, 0, 1, 0, 1>(7),
-        XCAND(400), XCAND(480), XCAND(576), XCAND(640), XCAND(720), XCAND(768), XCAND(960),
+        make_entry<400, kContiguous, StC64, 8, kC64, 0, 0, 0, 1, 1>(3), make_entry<480, kContiguous, StC64, 8, kC64, 0, 0, 0, 1, 1>(3),
         make_real_entry<256, StC64, 8, kC64, 1>(), make_real_entry<512, StC64, 8, kC64, 1>(),
     };
 }

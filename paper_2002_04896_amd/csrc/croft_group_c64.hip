@@ -1,0 +1,38 @@
+// croft_group_c64.hip -- complex64: the passes of croft_group.h (several stages
+// per register group), and the short 2^a 3^b 5^c lengths on the stage-by-stage
+// kernels.
+#include "croft_group.h"
+
+namespace croft {
+namespace dev {
+
+// strided above 240 and contiguous above 480; below, the stage-by-stage tiles
+// are as fast or faster.  Contiguous lines shorter than 75 and strided ones
+// shorter than 18 stay on the runtime-radix kernel.
+#define STRIDED(N) make_group_entry<N, StC64, 8, kC64, kStrided>(0),
+#define SHORT(N) make_entry<N, kStrided, StC64, 8, kC64>(0),
+#define LINES(N) make_entry<N, kContiguous, StC64, 8, kC64>(0),
+#define GLINES(N) make_group_entry<N, StC64, 8, kC64, kContiguous>(0),
+// contiguous 3: non-temporal, numbered as in croft_entries_c64.hip
+#define NTLINES(N) make_group_entry<N, StC64, 8, kC64, kContiguous, 1>(3),
+
+std::vector<Entry> group_entries_c64() {
+    return {
+        CROFT_GROUP_LONG(STRIDED)
+        // 384: 8, beside the candidates of croft_entries_c64.hip (174/136 us against 182/148)
+        make_group_entry<384, StC64, 8, kC64, kStrided>(8),
+        CROFT_GROUP_SHORT(SHORT)
+        LINES(75) LINES(81) LINES(90) LINES(108) LINES(125) LINES(135) LINES(144) LINES(150) LINES(162) LINES(180)
+        LINES(216) LINES(225) LINES(243) LINES(250) LINES(270) LINES(300) LINES(324) LINES(375) LINES(405) LINES(432)
+        LINES(450)
+        // contiguous, 0.8 GB moved (us, plain; non-temporal): 576 150, 148 (188 stage by stage), 864 149
+        // (178), 960 146, 143 (157)
+        GLINES(486) GLINES(500) GLINES(540) GLINES(576) GLINES(600) GLINES(625) GLINES(640) GLINES(648) GLINES(675)
+        GLINES(720) GLINES(729) GLINES(750) GLINES(768) GLINES(800) GLINES(810) GLINES(864) GLINES(900) GLINES(960)
+        GLINES(972) GLINES(1000)
+        NTLINES(576) NTLINES(640) NTLINES(720) NTLINES(768) NTLINES(960)
+    };
+}
+
+}  // namespace dev
+}  // namespace croft

@@ -45,6 +45,7 @@ struct KernelConfig {
     int plain = -1;                  // non-temporal or whole-tile: the candidate to run instead where
                                      // rows are not whole 128-byte lines or tiles are not whole
     bool whole_tiles = false;        // needs es to be a multiple of the lines per tile
+    bool one_tile = false;           // does not loop over tiles: one block per tile whatever grid_waves says
     int threads_per_line = 0;        // T
     int lines = 0;                   // L, lines per block
     int block = 0;                   // T * L

@@ -15,6 +15,13 @@ std::vector<Entry> entries_c64();
 std::vector<Entry> entries_c128();
 std::vector<Entry> entries_c16f();
 std::vector<Entry> entries_c16b();
+// the lengths of croft_group.h, likewise
+std::vector<Entry> group_entries_c64();
+std::vector<Entry> group_entries_c128();
+std::vector<Entry> group_entries_c16f();
+std::vector<Entry> group_entries_c16b();
+std::vector<Entry> group_entries_c16f_x();
+std::vector<Entry> group_entries_c16b_x();
 }  // namespace dev
 using namespace dev;
 namespace {
@@ -254,7 +261,8 @@ __global__ void __launch_bounds__(256) fft_generic_conv(const PassArgs a) {
 const std::vector<Entry> &table() {
     static const std::vector<Entry> t = [] {
         std::vector<Entry> v;
-        for (auto f : {entries_c64, entries_c128, entries_c16f, entries_c16b}) {
+        for (auto f : {entries_c64, entries_c128, entries_c16f, entries_c16b, group_entries_c64, group_entries_c128,
+                       group_entries_c16f, group_entries_c16b, group_entries_c16f_x, group_entries_c16b_x}) {
             std::vector<Entry> e = f();
             v.insert(v.end(), e.begin(), e.end());
         }
@@ -328,6 +336,7 @@ bool select_kernel(int n, int kind, int dtype, bool force_generic, int cand, Ker
             cfg->candidate = pick->cand;
             cfg->plain = pick->plain;
             cfg->whole_tiles = pick->whole_tiles;
+            cfg->one_tile = pick->one_tile;
             cfg->threads_per_line = pick->T;
             cfg->lines = pick->L;
             cfg->block = pick->block;
@@ -352,6 +361,7 @@ bool select_kernel(int n, int kind, int dtype, bool force_generic, int cand, Ker
         cfg->candidate = 0;
         cfg->plain = -1;
         cfg->whole_tiles = false;
+        cfg->one_tile = false;
         cfg->threads_per_line = T;
         cfg->lines = L;
         cfg->block = ((T * L + 63) / 64) * 64;
@@ -392,6 +402,7 @@ bool select_kernel(int n, int kind, int dtype, bool force_generic, int cand, Ker
     cfg->candidate = 0;
     cfg->plain = -1;
     cfg->whole_tiles = false;
+    cfg->one_tile = false;
     cfg->threads_per_line = T;
     cfg->lines = L;
     cfg->block = ((T * L + 63) / 64) * 64;
@@ -409,7 +420,7 @@ long long pass_tiles(const PassLaunch &pl) {
 
 long long pass_blocks(const PassLaunch &pl) {
     long long blocks = pass_tiles(pl);
-    if (!pl.cfg.generic && pl.cfg.resident > 0 && pl.cfg.grid_waves > 0)
+    if (!pl.cfg.generic && !pl.cfg.one_tile && pl.cfg.resident > 0 && pl.cfg.grid_waves > 0)
         blocks = std::min<long long>(blocks, (long long)pl.cfg.resident * pl.cfg.grid_waves);
     return blocks;
 }

@@ -14,7 +14,7 @@
 // per-axis built-in choices, the built-in table below (measured on an MI355X
 // with CROFT_MEASURE on cubic grids; kinds 2 and 3, the real x pass and the
 // fused multiply pass, on real and convolution plans of cubic grids), then
-// candidate 0 with one resident wave.  At each step an entry for the pass's
+// candidate 0 on the grid size the caller starts from.  At each step an entry for the pass's
 // axis comes before one for any axis.
 #include <cstdio>
 #include <cstdlib>
@@ -32,23 +32,20 @@ struct Builtin {
 // n kind dtype candidate waves
 const Builtin kBuiltin[] = {
     // complex64 (384: from a sweep of the 384^3 grid, too large for the
-    // Infinity Cache: the non-temporal contiguous tile, x 186 -> 163 us; the
-    // 32-line wide strided tile on one wave of resident blocks, y 212 -> 173
-    // and z 222 -> 176 us, both directions)
+    // Infinity Cache: the non-temporal contiguous tile, x 186 -> 163 us;
+    // strided, the grouped stages, 174/136 us against 182/148 for the 32-line
+    // wide tile (0.8 GB moved, rows of 360 and of 36000 elements))
     {32, 0, 0, 0, 1}, {32, 1, 0, 0, 1}, {48, 0, 0, 0, 0}, {48, 1, 0, 0, 2}, {60, 0, 0, 0, 4}, {60, 1, 0, 0, 0},
     {64, 0, 0, 0, 4}, {64, 1, 0, 0, 4}, {72, 0, 0, 0, 1}, {72, 1, 0, 0, 0}, {80, 0, 0, 0, 0}, {80, 1, 0, 0, 4},
     {96, 0, 0, 0, 1}, {96, 1, 0, 0, 1}, {100, 0, 0, 0, 2}, {100, 1, 0, 0, 4}, {128, 0, 0, 1, 2},
-    {128, 1, 0, 5, 1}, {256, 0, 0, 1, 0}, {256, 1, 0, 1, 0}, {384, 0, 0, 3, 0}, {384, 1, 0, 2, 1},
+    {128, 1, 0, 5, 1}, {256, 0, 0, 1, 0}, {256, 1, 0, 1, 0}, {384, 0, 0, 3, 0}, {384, 1, 0, 8, 0},
     // (the real x pass of the 512^3 real grid, length 256 above: the non-temporal
     // candidate, forward 0.613 -> 0.587 ms, backward 0.675 -> 0.640, convolution
     // 1.207 -> 1.194)
-    // complex64 at the larger compiled 2^a 3^b 5^c lengths (one forward sweep of
-    // n^3): the streaming contiguous tile for x except at 576; the strided tile
-    // in the XCD-contiguous order where it pays (576: 2.80 -> 2.22 ms, 640:
-    // 4.15 -> 3.16, 720: 5.76 -> 5.52, 768: 6.42 -> 4.89, 960: 12.70 -> 11.43)
-    {400, 0, 0, 3, 0}, {480, 0, 0, 3, 0}, {576, 1, 0, 6, 0}, {640, 0, 0, 3, 0}, {640, 1, 0, 6, 0},
-    {720, 0, 0, 3, 0}, {720, 1, 0, 7, 0}, {768, 0, 0, 3, 0}, {768, 1, 0, 6, 0}, {960, 0, 0, 3, 0},
-    {960, 1, 0, 7, 0},
+    // complex64 at the larger compiled 2^a 3^b 5^c lengths: the streaming
+    // contiguous tile for x (strided: the grouped stages, their only candidate)
+    {400, 0, 0, 3, 0}, {480, 0, 0, 3, 0}, {576, 0, 0, 3, 0}, {640, 0, 0, 3, 0}, {720, 0, 0, 3, 0}, {768, 0, 0, 3, 0},
+    {960, 0, 0, 3, 0},
     {512, 0, 0, 3, 0}, {512, 1, 0, 4, 4}, {1024, 0, 0, 3, 0}, {1024, 1, 0, 7, 1}, {32, 2, 0, 0, 0},
     {64, 2, 0, 0, 2}, {64, 3, 0, 0, 2}, {128, 2, 0, 0, 1}, {128, 3, 0, 0, 2}, {256, 2, 0, 1, 0},
     {256, 3, 0, 0, 1}, {512, 3, 0, 0, 2},
@@ -62,35 +59,23 @@ const Builtin kBuiltin[] = {
     {32, 0, 1, 0, 4}, {32, 1, 1, 0, 0}, {48, 0, 1, 0, 2}, {48, 1, 1, 0, 4}, {60, 0, 1, 0, 2}, {60, 1, 1, 0, 2},
     {64, 0, 1, 0, 0}, {64, 1, 1, 0, 4}, {72, 0, 1, 0, 1}, {72, 1, 1, 0, 0}, {80, 0, 1, 0, 1}, {80, 1, 1, 0, 0},
     {96, 0, 1, 0, 2}, {96, 1, 1, 0, 1}, {100, 0, 1, 0, 4}, {100, 1, 1, 0, 1}, {128, 0, 1, 3, 2},
-    {128, 1, 1, 5, 4}, {256, 0, 1, 3, 0}, {256, 1, 1, 5, 0}, {384, 0, 1, 0, 0}, {384, 1, 1, 0, 2},
+    {128, 1, 1, 5, 4}, {256, 0, 1, 3, 0}, {256, 1, 1, 5, 0}, {384, 0, 1, 0, 0},
     // complex128 at the larger compiled lengths (one forward sweep of n^3): the
-    // streaming x tile and the XCD-ordered strided tile with prefetch (640:
-    // 7.43 -> 5.87 ms with the strided choice alone, 768: 12.80 -> 10.59);
-    // 720 keeps the default, which none of the others beat
-    {400, 0, 1, 3, 0}, {400, 1, 1, 7, 0}, {480, 0, 1, 3, 0}, {480, 1, 1, 7, 0}, {576, 0, 1, 3, 0},
-    {576, 1, 1, 7, 0}, {640, 0, 1, 3, 0}, {640, 1, 1, 7, 0}, {768, 0, 1, 3, 0}, {768, 1, 1, 7, 0},
+    // streaming x tile; 720 keeps the default, which it did not beat
+    {400, 0, 1, 3, 0}, {480, 0, 1, 3, 0}, {576, 0, 1, 3, 0}, {640, 0, 1, 3, 0}, {768, 0, 1, 3, 0},
     {512, 0, 1, 3, 0}, {512, 1, 1, 4, 2}, {1024, 0, 1, 2, 0}, {1024, 1, 1, 5, 0}, {32, 2, 1, 0, 2},
     {64, 2, 1, 0, 1}, {64, 3, 1, 0, 0}, {128, 2, 1, 0, 1}, {128, 3, 1, 1, 1}, {256, 2, 1, 0, 2},
     {256, 3, 1, 0, 2}, {512, 3, 1, 0, 1},
-    // FP16 storage (400-768: the XCD-ordered strided tile, one FP16 forward
-    // sweep, BF16 the same: 640^3 3.70 -> 2.56 ms, 768^3 5.80 -> 4.00;
-    // 512 x: the non-temporal contiguous tile on four waves of
-    // resident blocks, 0.217 -> 0.195 ms in both directions; the same for BF16)
-    {32, 0, 2, 0, 2}, {32, 1, 2, 0, 0}, {48, 0, 2, 0, 0}, {48, 1, 2, 0, 2}, {60, 0, 2, 0, 1}, {60, 1, 2, 0, 0},
-    {64, 0, 2, 0, 0}, {64, 1, 2, 0, 1}, {72, 0, 2, 0, 2}, {72, 1, 2, 0, 0}, {80, 0, 2, 0, 4}, {80, 1, 2, 0, 2},
-    {96, 0, 2, 0, 4}, {96, 1, 2, 0, 0}, {100, 0, 2, 0, 1}, {100, 1, 2, 0, 4}, {128, 0, 2, 1, 1},
-    {128, 1, 2, 1, 4}, {256, 0, 2, 1, 0}, {256, 1, 2, 2, 1}, {384, 0, 2, 0, 0}, {384, 1, 2, 0, 1},
-    {512, 0, 2, 3, 4}, {512, 1, 2, 6, 1}, {1024, 0, 2, 3, 4}, {1024, 1, 2, 7, 1},
-    {400, 1, 2, 6, 0}, {576, 1, 2, 6, 0}, {640, 1, 2, 6, 0}, {720, 0, 2, 3, 0}, {720, 1, 2, 7, 0},
-    {768, 1, 2, 7, 0},
+    // FP16 storage (strided 128 and 256: the grouped stages; 512 x: the
+    // non-temporal contiguous tile on four waves of resident blocks, 0.217 ->
+    // 0.195 ms in both directions; the same for BF16)
+    {32, 0, 2, 0, 2}, {48, 0, 2, 0, 0}, {60, 0, 2, 0, 1}, {64, 0, 2, 0, 0}, {128, 0, 2, 1, 1}, {128, 1, 2, 6, 0},
+    {256, 0, 2, 1, 0}, {256, 1, 2, 6, 0}, {512, 0, 2, 3, 4}, {512, 1, 2, 6, 1}, {1024, 0, 2, 3, 4},
+    {1024, 1, 2, 7, 1},
     // BF16 storage
-    {32, 0, 3, 0, 0}, {32, 1, 3, 0, 2}, {48, 0, 3, 0, 2}, {48, 1, 3, 0, 2}, {60, 0, 3, 0, 4}, {60, 1, 3, 0, 1},
-    {64, 0, 3, 0, 2}, {64, 1, 3, 0, 4}, {72, 0, 3, 0, 4}, {72, 1, 3, 0, 4}, {80, 0, 3, 0, 1}, {80, 1, 3, 0, 2},
-    {96, 0, 3, 0, 0}, {96, 1, 3, 0, 2}, {100, 0, 3, 0, 2}, {100, 1, 3, 0, 0}, {128, 0, 3, 1, 2},
-    {128, 1, 3, 1, 0}, {256, 0, 3, 1, 0}, {256, 1, 3, 2, 1}, {384, 0, 3, 0, 0}, {384, 1, 3, 0, 1},
-    {512, 0, 3, 3, 4}, {512, 1, 3, 6, 1}, {1024, 0, 3, 3, 4}, {1024, 1, 3, 7, 1},
-    {400, 1, 3, 6, 0}, {576, 1, 3, 6, 0}, {640, 1, 3, 6, 0}, {720, 0, 3, 3, 0}, {720, 1, 3, 7, 0},
-    {768, 1, 3, 7, 0},
+    {32, 0, 3, 0, 0}, {48, 0, 3, 0, 2}, {60, 0, 3, 0, 4}, {64, 0, 3, 0, 2}, {128, 0, 3, 1, 2}, {128, 1, 3, 6, 0},
+    {256, 0, 3, 1, 0}, {256, 1, 3, 6, 0}, {512, 0, 3, 3, 4}, {512, 1, 3, 6, 1}, {1024, 0, 3, 3, 4},
+    {1024, 1, 3, 7, 1},
 };
 
 // Forward-only choices, looked up before the table above by forward plans:

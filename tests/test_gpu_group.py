@@ -1,0 +1,74 @@
+"""The passes that run several stages per register group, at the lengths
+where their shapes change: one group, two and three, with and without the
+padded or split exchange, first and last length of each range, and tiles that
+are not whole.  The grouped stages are the runtime-radix kernel's, butterfly
+for butterfly, so the outputs must be its bits; the oracle comparison keeps
+the suite's tolerances (unit roundoff times a few stages, far below them)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2002_04896_amd as croft
+from paper_2002_04896_amd import synth
+from gpu_helpers import HALF_KIND, TOL, run_fft, run_half
+
+pytestmark = pytest.mark.gpu
+
+C64, C128, F16, BF16 = croft.CROFT_C64, croft.CROFT_C128, croft.CROFT_C16F, croft.CROFT_C16B
+FWD, BWD = croft.CROFT_FORWARD, croft.CROFT_BACKWARD
+GENERIC = croft.CROFT_FORCE_GENERIC
+
+# (nz, ny, nx); strided axes beside rows that are not a multiple of a tile
+SHAPES = [(18, 243, 5), (1000, 3, 17), (972, 2, 3), (960, 1, 33), (3, 900, 9), (2, 810, 4), (720, 2, 5), (25, 54, 75),
+          (2, 3, 1000), (3, 2, 486), (2, 2, 720), (384, 3, 6), (5, 480, 7), (128, 4, 9), (256, 2, 11), (81, 3, 972)]
+
+
+@pytest.mark.parametrize("direction", [FWD, BWD], ids=["fwd", "bwd"])
+@pytest.mark.parametrize("dtype", [C64, C128], ids=["c64", "c128"])
+@pytest.mark.parametrize("shape", SHAPES, ids=str)
+def test_matches_oracle_and_runtime_radix_bits(shape, dtype, direction):
+    x = synth.normal_c(shape, seed=51)
+    seen, y, after = run_fft(x, dtype, direction)
+    assert oracle.rel_l2(y, oracle.dft3d(seen, direction)) <= TOL[dtype]
+    np.testing.assert_array_equal(after, seen)
+    _, g, _ = run_fft(x, dtype, direction, flags=GENERIC)
+    np.testing.assert_array_equal(y, g)
+
+
+@pytest.mark.parametrize("dtype", [F16, BF16], ids=["f16", "bf16"])
+@pytest.mark.parametrize("shape", SHAPES, ids=str)
+def test_half_storage_matches_oracle_and_runtime_radix_bits(shape, dtype):
+    kind = HALF_KIND[dtype]
+    nz, ny, nx = shape
+    data, e = synth.quantize_half(synth.normal_c(shape, seed=52), kind)
+    for direction in (FWD, BWD):
+        out, oe = run_half(data, e, dtype, direction)
+        exact = oracle.dft3d(oracle.decode_half(data, e, kind, 0), direction)
+        assert oracle.rel_l2(oracle.decode_half(out, oe, kind, 2), exact) <= TOL[dtype]
+        d_in = torch.from_numpy(np.ascontiguousarray(data.view(np.int16))).cuda()
+        d_out, d_e = torch.empty_like(d_in), torch.empty((ny, nx), dtype=torch.int8, device="cuda")
+        plan = croft.croft_plan_create_ex(nx, ny, nz, dtype, direction, GENERIC, 1)
+        croft.croft_execute_scaled(plan, d_in, torch.from_numpy(e).cuda(), d_out, d_e)
+        torch.cuda.synchronize()
+        croft.croft_plan_destroy(plan)
+        np.testing.assert_array_equal(d_out.cpu().numpy().view(np.uint16), out)
+        np.testing.assert_array_equal(d_e.cpu().numpy(), oe)
+
+
+def test_one_block_per_tile_whatever_the_wisdom_says(tmp_path, monkeypatch):
+    """These kernels do not loop over tiles: a persistent grid named in a
+    wisdom file must not leave tiles undone.  2400 tiles of 243-point lines,
+    more than one wave of resident blocks."""
+    wisdom = tmp_path / "w.txt"
+    monkeypatch.setenv("CROFT_WISDOM", str(wisdom))
+    x = torch.randn((600, 243, 64), dtype=torch.complex64, device="cuda")
+    outs = []
+    for line, flags in (("", GENERIC), ("243 1 0 0 1 1\n", 0)):
+        wisdom.write_text(line)
+        plan = croft.croft_plan_create_ex(64, 243, 600, C64, FWD, flags, 1)
+        outs.append(torch.full_like(x, complex(float("nan"), 0)))
+        croft.croft_execute(plan, x, outs[-1])
+        torch.cuda.synchronize()
+        croft.croft_plan_destroy(plan)
+    assert torch.equal(*outs)
