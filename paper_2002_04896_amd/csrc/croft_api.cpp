@@ -55,7 +55,7 @@ struct croft_plan {
     std::vector<size_t> offsets;  // element offsets, grids.size() + 1 entries
     // per grid: the pass list of the plain schedule
     std::vector<std::vector<PassLaunch>> passes;
-    std::map<int, void *> twiddles;  // length -> device table
+    std::map<int, void *> twiddles;  // length -> device table; -length -> the table in the stages' order
     std::map<int, std::pair<void *, void *>> bluestein;  // length -> (chirp, kernel DFT)
     int8_t *e1 = nullptr, *e2 = nullptr;  // half storage: exponents after x and y passes
     int8_t *scratch = nullptr;            // half storage: this device's static scratch array
@@ -499,18 +499,32 @@ int prepare_kernel(KernelConfig *cfg) {
 int attach_resources(croft_plan *p) {
     hipError_t e;
     const bool dbl = p->dtype == CROFT_C128;
-    // the table w_n^m, m < n, of a length, uploaded once per plan
-    auto table = [&](int n, const void **out) -> int {
-        if (!p->twiddles.count(n)) {
-            std::vector<double> w(2 * (size_t)n);
-            twiddles_fp64(n, w.data());
+    // the table w_n^m, m < n, of a length (staged: in the order of the stages'
+    // reads), uploaded once per plan
+    auto table = [&](int n, const void **out, bool staged = false) -> int {
+        const int key = staged ? -n : n;
+        if (!p->twiddles.count(key)) {
+            std::vector<double> w;
+            if (staged) {
+                w = stage_twiddles_fp64(n);
+            } else {
+                w.resize(2 * (size_t)n);
+                twiddles_fp64(n, w.data());
+            }
+            if (w.empty()) {  // one stage: no twiddles to read
+                int radix[kMaxStages];
+                if (factorize(n, radix) != 1 && n != 1)
+                    return fail(CROFT_ERR_INTERNAL, "no stage twiddles for length %d", n);
+                *out = nullptr;
+                return CROFT_SUCCESS;
+            }
             void *d = nullptr;
-            const size_t bytes = (size_t)n * compute_bytes(p->dtype);
+            const size_t bytes = w.size() / 2 * compute_bytes(p->dtype);
             if ((e = plan_alloc(p, &d, bytes)) != hipSuccess) {
                 (void)hipGetLastError();
                 return fail(CROFT_ERR_OUT_OF_MEMORY, "twiddle table: %s", hipGetErrorString(e));
             }
-            p->twiddles[n] = d;
+            p->twiddles[key] = d;
             p->work_bytes += bytes;
             if (dbl) {
                 e = hipMemcpy(d, w.data(), bytes, hipMemcpyHostToDevice);
@@ -521,7 +535,7 @@ int attach_resources(croft_plan *p) {
             }
             if (e != hipSuccess) return fail_hip(e, "twiddle upload");
         }
-        *out = p->twiddles[n];
+        *out = p->twiddles[key];
         return CROFT_SUCCESS;
     };
     // Bluestein's chirp and kernel DFT of a length (convolution length m)
@@ -563,12 +577,19 @@ int attach_resources(croft_plan *p) {
     for (auto &ps : p->passes) {
         for (PassLaunch &pl : ps) {
             int rc;
-            pl.tw = nullptr;
+            pl.tw = pl.tw_stages = nullptr;
             if (pl.cfg.bluestein) {
-                if ((rc = table(pl.cfg.bluestein, &pl.tw)) != CROFT_SUCCESS) return rc;
+                if ((rc = table(pl.cfg.bluestein, &pl.tw_stages, true)) != CROFT_SUCCESS) return rc;
                 if ((rc = blue(pl.n, pl.cfg.bluestein, &pl)) != CROFT_SUCCESS) return rc;
-            } else if (pl.n > 1 && (rc = table(pl.n, &pl.tw)) != CROFT_SUCCESS) {
-                return rc;
+            } else if (pl.n > 1) {
+                // both where the autotuner may change the kernel, and for the
+                // batched kernel, which reads the first
+                const bool measure = (p->flags & CROFT_MEASURE) != 0;
+                if ((!pl.cfg.stage_table || measure || p->batched) && (rc = table(pl.n, &pl.tw)) != CROFT_SUCCESS)
+                    return rc;
+                if ((pl.cfg.stage_table || (measure && !pl.cfg.generic)) &&
+                    (rc = table(pl.n, &pl.tw_stages, true)) != CROFT_SUCCESS)
+                    return rc;
             }
             if (pl.kind == kRealX && (rc = table(2 * pl.n, &pl.tw2)) != CROFT_SUCCESS) return rc;
             if ((rc = prepare_kernel(&pl.cfg)) != CROFT_SUCCESS) return rc;

@@ -1739,7 +1739,7 @@ struct Entry {
     RPlan plan;
     int plain = -1;  // non-temporal candidates: the candidate without the hint
     bool whole_tiles = false;  // runs only where every tile is whole (es a multiple of L)
-    bool one_tile = false;     // the kernel does not loop: one block per tile always
+    bool one_tile = false;     // grouped stages: one block per tile always, twiddles in the stages' order
 };
 
 // An entry whose kernel uses the non-temporal hint, with the candidate index

@@ -83,16 +83,20 @@ constexpr GroupPlan make_groups(const RPlan &p, int emax) {
 // Launch shape: L lines per block, T threads per line, at most EMAX elements
 // held by a thread.  One block per tile (the kernel does not loop): several
 // small blocks on a CU overlap one tile's loads with another's stages.
-template <int N, int KIND, int LREQ, int EMAX, int COMPUTE_BYTES, int SPLIT, int XO = 0, int NT = 0>
+template <int N, int KIND, int LREQ, int EMAX, int COMPUTE_BYTES, int SPLIT, int XO = 0, int NT = 0,
+          int TREQ = 0>
 struct GCfg {
+    static constexpr int kCB = COMPUTE_BYTES;
     static constexpr bool kXO = XO != 0;
     static constexpr bool kNT = NT != 0;
     static constexpr RPlan plan = make_rplan(N);
     static constexpr GroupPlan groups = make_groups(plan, EMAX);
     static_assert(groups.K >= 1, "the length has a cut");
-    static constexpr int T = groups.T;
+    static constexpr int T = TREQ > 0 ? TREQ : groups.T;
     static constexpr int L = LREQ;
     static constexpr int kBlock = T * L;
+    // lines never straddle a wavefront: exchanges sync per wave, not per block
+    static constexpr bool kWaveSync = KIND == kContiguous && T <= 64 && 64 % T == 0;
     static constexpr bool kSplit = SPLIT != 0;   // the real parts, then the imaginary parts, through LDS
     static constexpr int kTwN = tw_offset(plan, plan.S);
     static constexpr int size(int g) { return group_size(plan, groups.first[g], groups.first[g + 1]); }
@@ -138,6 +142,9 @@ __device__ __forceinline__ void group_stages(cx<R> *v, const cx<R> *tws, int k) 
                 Dft<RAD, R>::run(u);
 #pragma unroll
                 for (int q = 0; q < RAD; ++q) w[(s + NSUB * q) * H + m] = u[q];
+                // keep the next butterflies' twiddle reads below this one:
+                // bounds the registers live beside a large group
+                if constexpr (NSUB * G >= 64) __builtin_amdgcn_sched_barrier(0);
             }
         }
 #pragma unroll
@@ -168,7 +175,7 @@ __device__ __forceinline__ void group_exchange(unsigned char *smem, int l, int t
     constexpr int kParts = Cfg::kSplit ? 2 : 1;
 #pragma unroll
     for (int part = 0; part < kParts; ++part) {
-        __syncthreads();  // the previous readers of the area are done
+        stage_sync<Cfg::kWaveSync>();  // the previous readers of the area are done
 #pragma unroll
         for (int b = 0; b < B; ++b) {
             const int j = t + b * T;
@@ -184,7 +191,7 @@ __device__ __forceinline__ void group_exchange(unsigned char *smem, int l, int t
                 }
             }
         }
-        __syncthreads();
+        stage_sync<Cfg::kWaveSync>();
 #pragma unroll
         for (int b = 0; b < BN; ++b) {
             const int j = t + b * T;
@@ -290,7 +297,7 @@ __global__ void __launch_bounds__(Cfg::kBlock) fft_group(const PassArgs a) {
     }
     if constexpr (Cfg::kTwN > 0) {
         const cx<R> *W = reinterpret_cast<const cx<R> *>(a.tw);
-        for (int i = tid; i < Cfg::kTwN; i += Cfg::kBlock) tws[i] = W[tw_source<Cfg>(i)];
+        for (int i = tid; i < Cfg::kTwN; i += Cfg::kBlock) tws[i] = W[i];
     }
     if constexpr (St::kHalf && T > 1) {
         if (tid < L) red[tid] = 0u;

@@ -46,6 +46,7 @@ struct KernelConfig {
                                      // rows are not whole 128-byte lines or tiles are not whole
     bool whole_tiles = false;        // needs es to be a multiple of the lines per tile
     bool one_tile = false;           // does not loop over tiles: one block per tile whatever grid_waves says
+    bool stage_table = false;        // twiddles in the order of the stages' reads (stage_twiddles_fp64)
     int threads_per_line = 0;        // T
     int lines = 0;                   // L, lines per block
     int block = 0;                   // T * L
@@ -96,6 +97,7 @@ struct PassLaunch {
     long long nw = 1;      // strided: number of w
     KernelConfig cfg;
     const void *tw = nullptr;  // device twiddle table of length n (dtype's compute type)
+    const void *tw_stages = nullptr;  // the same in the order of the stages' reads, for cfg.stage_table kernels
     const void *tw2 = nullptr; // kRealX: device twiddle table of length 2 n
     ExpMap em;
     const void *chirp = nullptr;  // Bluestein: exp(-pi i j^2 / n), j < n
@@ -198,6 +200,9 @@ int factorize(int n, int *radix);  // returns stage count, 0 if unsupported
 // Forward twiddles w[m] = exp(-2 pi i m / n), m < n, computed in FP64 with
 // octant symmetry, written as interleaved doubles (2n values).
 void twiddles_fp64(int n, double *out);
+// The same values in the order of the stages' reads (interleaved doubles;
+// empty for a length of one stage): the table of the grouped kernels.
+std::vector<double> stage_twiddles_fp64(int n);
 // out[i] = in[i] rounded to nearest even FP32 (the tables of FP32-compute
 // plans are the FP64 values rounded once).
 void round_to_fp32(const double *in, size_t count, float *out);

@@ -336,7 +336,7 @@ bool select_kernel(int n, int kind, int dtype, bool force_generic, int cand, Ker
             cfg->candidate = pick->cand;
             cfg->plain = pick->plain;
             cfg->whole_tiles = pick->whole_tiles;
-            cfg->one_tile = pick->one_tile;
+            cfg->one_tile = cfg->stage_table = pick->one_tile;
             cfg->threads_per_line = pick->T;
             cfg->lines = pick->L;
             cfg->block = pick->block;
@@ -362,6 +362,7 @@ bool select_kernel(int n, int kind, int dtype, bool force_generic, int cand, Ker
         cfg->plain = -1;
         cfg->whole_tiles = false;
         cfg->one_tile = false;
+        cfg->stage_table = true;
         cfg->threads_per_line = T;
         cfg->lines = L;
         cfg->block = ((T * L + 63) / 64) * 64;
@@ -402,7 +403,7 @@ bool select_kernel(int n, int kind, int dtype, bool force_generic, int cand, Ker
     cfg->candidate = 0;
     cfg->plain = -1;
     cfg->whole_tiles = false;
-    cfg->one_tile = false;
+    cfg->one_tile = cfg->stage_table = false;
     cfg->threads_per_line = T;
     cfg->lines = L;
     cfg->block = ((T * L + 63) / 64) * 64;
@@ -431,7 +432,7 @@ hipError_t launch_pass(const PassLaunch &pl, int dtype, const void *in, void *ou
     PassArgs a;
     a.in = in;
     a.out = out;
-    a.tw = pl.tw;
+    a.tw = pl.cfg.stage_table ? pl.tw_stages : pl.tw;
     a.tw2 = pl.tw2;
     a.chirp = pl.chirp;
     a.bhat = pl.bhat;

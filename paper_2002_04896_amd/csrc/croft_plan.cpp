@@ -17,13 +17,14 @@ bool smooth_length(int n) {
 
 // Same factorisation rule as the kernels' compile-time plans: the 5s, the 3s,
 // then the power of two as radix-8 stages plus one radix-4 or radix-16 stage
-// for the remainder (a lone 2 or 4 for n = 2, 4).
-int factorize(int n, int *radix) {
-    if (!smooth_length(n)) return 0;
+// for the remainder (a lone 2 or 4 for n = 2, 4).  Any n = 2^a 3^b 5^c (a
+// Bluestein convolution may be longer than the longest line); 0 for others.
+static int stage_radices(int n, int *radix) {
     int m = n, c5 = 0, c3 = 0, a2 = 0, s = 0;
     while (m % 5 == 0) { m /= 5; ++c5; }
     while (m % 3 == 0) { m /= 3; ++c3; }
     while (m % 2 == 0) { m /= 2; ++a2; }
+    if (m != 1) return 0;
     for (int i = 0; i < c5; ++i) radix[s++] = 5;
     for (int i = 0; i < c3; ++i) radix[s++] = 3;
     const int k = a2 / 3, rem = a2 % 3;
@@ -37,6 +38,8 @@ int factorize(int n, int *radix) {
     }
     return s;
 }
+
+int factorize(int n, int *radix) { return smooth_length(n) ? stage_radices(n, radix) : 0; }
 
 // w[m] = exp(-2 pi i m / n).  The angle 2 pi m / n is split into q quarter
 // turns plus phi = (pi/2) r / n with r = 4m - q n in [0, n); phi is folded into
@@ -70,6 +73,29 @@ void twiddles_fp64(int n, double *out) {
         out[2 * m] = C;
         out[2 * m + 1] = -S;
     }
+}
+
+// The same values in the order the stages read them: for every stage s > 0
+// of radix R with span Ns, entry (q, k) = w_n^(q k n / (Ns R)), q = 1 .. R - 1,
+// k = 0 .. Ns - 1, k fastest.
+std::vector<double> stage_twiddles_fp64(int n) {
+    int radix[kMaxStages] = {};
+    const int stages = stage_radices(n, radix);
+    std::vector<double> w(2 * (size_t)n), out;
+    twiddles_fp64(n, w.data());
+    int ns = 1;
+    for (int s = 0; s < stages; ++s) {
+        const int r = radix[s];
+        if (s > 0)
+            for (int q = 1; q < r; ++q)
+                for (int k = 0; k < ns; ++k) {
+                    const size_t m = (size_t)q * k * (n / (ns * r));
+                    out.push_back(w[2 * m]);
+                    out.push_back(w[2 * m + 1]);
+                }
+        ns *= r;
+    }
+    return out;
 }
 
 // The FP64 values rounded once, to nearest even, to the FP32 the c64 and

@@ -72,3 +72,24 @@ def test_one_block_per_tile_whatever_the_wisdom_says(tmp_path, monkeypatch):
         torch.cuda.synchronize()
         croft.croft_plan_destroy(plan)
     assert torch.equal(*outs)
+
+
+# prime lengths for the convolution lengths 32 .. 4096 in 16-bit storage, on
+# the contiguous and the strided axes (n close to m / 2 and close to m / 4)
+@pytest.mark.parametrize("dtype", [F16, BF16], ids=["f16", "bf16"])
+@pytest.mark.parametrize("shape", [(11, 31, 17), (37, 3, 61), (5, 127, 67), (131, 2, 251), (3, 509, 7), (2, 257, 1021),
+                                   (1031, 3, 2), (2, 2, 2039), (1, 4093, 2), (1, 2, 4091)], ids=str)
+def test_bluestein_half_storage(shape, dtype):
+    kind = HALF_KIND[dtype]
+    data, e = synth.quantize_half(synth.normal_c(shape, seed=53), kind)
+    for direction in (FWD, BWD):
+        out, oe = run_half(data, e, dtype, direction)
+        exact = oracle.dft3d(oracle.decode_half(data, e, kind, 0), direction)
+        assert oracle.rel_l2(oracle.decode_half(out, oe, kind, 2), exact) <= TOL[dtype]
+
+
+@pytest.mark.parametrize("direction", [FWD, BWD], ids=["fwd", "bwd"])
+def test_longest_strided_convolution(direction):
+    x = synth.normal_c((2, 4093, 3), seed=54)
+    seen, y, _ = run_fft(x, C64, direction)
+    assert oracle.rel_l2(y, oracle.dft3d(seen, direction)) <= TOL[C64]
