@@ -55,8 +55,7 @@ struct croft_plan {
     std::vector<size_t> offsets;  // element offsets, grids.size() + 1 entries
     // per grid: the pass list of the plain schedule
     std::vector<std::vector<PassLaunch>> passes;
-    std::map<int, void *> twiddles;  // length -> device table; -length -> the table in the stages' order
-    std::map<int, std::pair<void *, void *>> bluestein;  // length -> (chirp, kernel DFT)
+    void *tables = nullptr;  // every twiddle, chirp and kernel DFT table of the passes
     int8_t *e1 = nullptr, *e2 = nullptr;  // half storage: exponents after x and y passes
     int8_t *scratch = nullptr;            // half storage: this device's static scratch array
     size_t work_bytes = 0;
@@ -139,6 +138,30 @@ int no_kernel(int n, int dtype) {
     return fail(CROFT_ERR_UNSUPPORTED_SIZE, "no kernel for length %d", n);
 }
 
+// True where the rows of a strided pass are not whole 128-byte lines.
+bool partial_lines(const PassLaunch &p, int dtype) { return (p.es * (long long)element_bytes(dtype)) % 128 != 0; }
+
+// The configuration a contiguous or strided pass starts from: a measured
+// choice; for FP32 and FP64 rows that are not whole lines the grouped stages,
+// whose tile order keeps the shared lines in one L2 (croft_group.h has the
+// figures); a built-in choice; else candidate 0, one block per tile (0.8 GB
+// moved, complex64, against one wave of resident blocks looping over the
+// tiles: strided 25 132 us against 159, 150 149 against 160, 300 contiguous
+// 141 against 164; below 24 MB level).
+void pass_choice(const PassLaunch &p, int dtype, int dir, int *cand, int *waves) {
+    const int axis = wisdom_axis(p.kind, p.axis);
+    *cand = *waves = 0;
+    if (wisdom_measured(p.n, p.kind, dtype, axis, cand, waves)) return;
+    if (p.kind == kStrided && !is_half(dtype) && partial_lines(p, dtype)) {
+        const int g = grouped_candidate(p.n, dtype);
+        if (g >= 0) {
+            *cand = g;
+            return;
+        }
+    }
+    wisdom_lookup(p.n, p.kind, dtype, dir, axis, cand, waves);
+}
+
 // Non-temporal stores of part of a 128-byte line cost a read-modify-write,
 // and partial non-temporal loads fetch their lines again: where the rows of
 // a strided pass are not whole lines (a real grid's half-spectrum y pass,
@@ -148,9 +171,8 @@ int no_kernel(int n, int dtype) {
 // LDS) gives way to its twin where the last tile of a row is partial.
 void plain_on_partial_lines(const PassLaunch &p, int dtype, KernelConfig *cfg) {
     if (p.kind != kStrided || cfg->generic || cfg->plain < 0) return;
-    const bool partial_lines = (p.es * (long long)element_bytes(dtype)) % 128 != 0;
     const bool partial_tiles = cfg->whole_tiles && p.es % cfg->lines != 0;
-    if (!partial_lines && !partial_tiles) return;
+    if (!partial_lines(p, dtype) && !partial_tiles) return;
     KernelConfig c;
     if (select_kernel(p.n, p.kind, dtype, false, cfg->plain, &c) && c.candidate == cfg->plain) *cfg = c;
 }
@@ -201,12 +223,8 @@ int build_passes(const Geometry &g, int dtype, int dir, int flags, std::vector<P
             p.nlines = p.es;
             p.nw = N / (p.es * n);
         }
-        // no measured choice: candidate 0, one block per tile (0.8 GB moved,
-        // complex64, against one wave of resident blocks looping over the
-        // tiles: strided 25 132 us against 159, 150 149 against 160, 300
-        // contiguous 141 against 164; below 24 MB level)
-        int cand = 0, waves = 0;
-        wisdom_lookup(n, p.kind, dtype, dir, wisdom_axis(p.kind, axis), &cand, &waves);
+        int cand, waves;
+        pass_choice(p, dtype, dir, &cand, &waves);
         if (!select_kernel(n, p.kind, dtype, (flags & CROFT_FORCE_GENERIC) != 0, cand, &p.cfg))
             return no_kernel(n, dtype);
         if (!lane_offset_fits(p, dtype) && !select_kernel(n, p.kind, dtype, true, 0, &p.cfg))
@@ -318,8 +336,7 @@ int build_real_passes(const Geometry &g, int dtype, int dir, int flags, std::vec
         p.es = axis == 1 ? h : h * g.ny;
         p.nlines = p.es;
         p.nw = axis == 1 ? g.nz : 1;
-        cand = waves = 0;
-        wisdom_lookup(n, kStrided, dtype, tune_dir, axis, &cand, &waves);
+        pass_choice(p, dtype, tune_dir, &cand, &waves);
         if (!select_kernel(n, kStrided, dtype, (flags & CROFT_FORCE_GENERIC) != 0, cand, &p.cfg))
             return no_kernel(n, dtype);
         if (!lane_offset_fits(p, dtype) && !select_kernel(n, kStrided, dtype, true, 0, &p.cfg))
@@ -352,7 +369,9 @@ int build_conv_passes(const Geometry &g, int dtype, int flags, std::vector<PassL
     c.kind = kConvZ;
     c.hx = (long long)g.nx / 2 + 1;
     int cand = 0, waves = 1;
-    wisdom_lookup(c.n, kConvZ, dtype, 0, -1, &cand, &waves);
+    if (!wisdom_lookup(c.n, kConvZ, dtype, 0, -1, &cand, &waves))
+        conv_choice(c.n, dtype, c.hx * g.ny * g.nz * (long long)element_bytes(dtype), partial_lines(c, dtype), &cand,
+                    &waves);
     const bool compiled = select_kernel(c.n, kConvZ, dtype, false, cand, &c.cfg);
     if ((!compiled || !lane_offset_fits(c, dtype)) && !select_generic_conv(c.n, dtype, &c.cfg))
         return fail(CROFT_ERR_UNSUPPORTED_SIZE,
@@ -438,11 +457,7 @@ hipError_t plan_alloc(croft_plan *p, void **ptr, size_t bytes) {
 
 void destroy_plan(croft_plan *p) {
     if (!p) return;
-    for (auto &kv : p->twiddles) (void)hipFree(kv.second);
-    for (auto &kv : p->bluestein) {
-        (void)hipFree(kv.second.first);
-        (void)hipFree(kv.second.second);
-    }
+    if (p->tables) (void)hipFree(p->tables);
     if (p->e1) (void)hipFree(p->e1);
     if (p->e2) (void)hipFree(p->e2);
     if (p->rwork) (void)hipFree(p->rwork);
@@ -499,102 +514,81 @@ int prepare_kernel(KernelConfig *cfg) {
 int attach_resources(croft_plan *p) {
     hipError_t e;
     const bool dbl = p->dtype == CROFT_C128;
-    // the table w_n^m, m < n, of a length (staged: in the order of the stages'
-    // reads), uploaded once per plan
-    auto table = [&](int n, const void **out, bool staged = false) -> int {
-        const int key = staged ? -n : n;
-        if (!p->twiddles.count(key)) {
-            std::vector<double> w;
-            if (staged) {
-                w = stage_twiddles_fp64(n);
-            } else {
-                w.resize(2 * (size_t)n);
-                twiddles_fp64(n, w.data());
-            }
-            if (w.empty()) {  // one stage: no twiddles to read
-                int radix[kMaxStages];
-                if (factorize(n, radix) != 1 && n != 1)
-                    return fail(CROFT_ERR_INTERNAL, "no stage twiddles for length %d", n);
-                *out = nullptr;
-                return CROFT_SUCCESS;
-            }
-            void *d = nullptr;
-            const size_t bytes = w.size() / 2 * compute_bytes(p->dtype);
-            if ((e = plan_alloc(p, &d, bytes)) != hipSuccess) {
-                (void)hipGetLastError();
-                return fail(CROFT_ERR_OUT_OF_MEMORY, "twiddle table: %s", hipGetErrorString(e));
-            }
-            p->twiddles[key] = d;
-            p->work_bytes += bytes;
-            if (dbl) {
-                e = hipMemcpy(d, w.data(), bytes, hipMemcpyHostToDevice);
-            } else {
-                std::vector<float> f(w.size());
-                round_to_fp32(w.data(), w.size(), f.data());
-                e = hipMemcpy(d, f.data(), bytes, hipMemcpyHostToDevice);
-            }
-            if (e != hipSuccess) return fail_hip(e, "twiddle upload");
-        }
-        *out = p->twiddles[key];
-        return CROFT_SUCCESS;
-    };
-    // Bluestein's chirp and kernel DFT of a length (convolution length m)
-    auto upload = [&](const std::vector<double> &v, void **out) -> int {
-        const size_t count = v.size() / 2;
-        const size_t bytes = count * compute_bytes(p->dtype);
-        if ((e = plan_alloc(p, out, bytes)) != hipSuccess) {
-            (void)hipGetLastError();
-            *out = nullptr;
-            return fail(CROFT_ERR_OUT_OF_MEMORY, "Bluestein table: %s", hipGetErrorString(e));
-        }
+    // every table of the plan (256-byte aligned) in one device allocation, filled
+    // by one copy: key (kind, length) -> byte offset.  Kinds: 0 w_n^m, m < n;
+    // 1 the same in the order of the stages' reads; 2 Bluestein's chirp and 3
+    // its kernel's DFT.
+    std::vector<char> host;
+    std::map<std::pair<int, int>, size_t> at;
+    auto append = [&](int kind, int n, const std::vector<double> &w) {
+        const size_t bytes = w.size() / 2 * compute_bytes(p->dtype);
+        const size_t off = host.size();
+        host.resize(off + (bytes + 255) / 256 * 256);
+        if (dbl) std::memcpy(host.data() + off, w.data(), bytes);
+        else round_to_fp32(w.data(), w.size(), reinterpret_cast<float *>(host.data() + off));
+        at[{kind, n}] = off;
         p->work_bytes += bytes;
-        if (dbl) {
-            e = hipMemcpy(*out, v.data(), bytes, hipMemcpyHostToDevice);
-        } else {
-            std::vector<float> f(v.size());
-            round_to_fp32(v.data(), v.size(), f.data());
-            e = hipMemcpy(*out, f.data(), bytes, hipMemcpyHostToDevice);
-        }
-        return e == hipSuccess ? CROFT_SUCCESS : fail_hip(e, "Bluestein table upload");
     };
-    auto blue = [&](int n, int m, PassLaunch *pl) -> int {
-        if (!p->bluestein.count(n)) {
-            std::vector<double> c(2 * (size_t)n), b(2 * (size_t)m);
-            bluestein_tables_fp64(n, m, c.data(), b.data());
-            std::pair<void *, void *> t{nullptr, nullptr};
-            int rc = upload(c, &t.first);
-            if (rc == CROFT_SUCCESS) rc = upload(b, &t.second);
-            if (rc != CROFT_SUCCESS) {
-                if (t.first) (void)hipFree(t.first);
-                return rc;
-            }
-            p->bluestein[n] = t;
-        }
-        pl->chirp = p->bluestein[n].first;
-        pl->bhat = p->bluestein[n].second;
+    auto twiddles = [&](int n) {
+        if (at.count({0, n})) return;
+        std::vector<double> w(2 * (size_t)n);
+        twiddles_fp64(n, w.data());
+        append(0, n, w);
+    };
+    auto stages = [&](int n) -> int {
+        if (at.count({1, n})) return CROFT_SUCCESS;
+        const std::vector<double> w = stage_twiddles_fp64(n);
+        int radix[kMaxStages];
+        if (w.empty() && n > 1 && factorize(n, radix) != 1)
+            return fail(CROFT_ERR_INTERNAL, "no stage twiddles for length %d", n);
+        if (!w.empty()) append(1, n, w);  // one stage: no twiddles to read
         return CROFT_SUCCESS;
     };
+    const bool measure = (p->flags & CROFT_MEASURE) != 0;
     for (auto &ps : p->passes) {
         for (PassLaunch &pl : ps) {
             int rc;
-            pl.tw = pl.tw_stages = nullptr;
             if (pl.cfg.bluestein) {
-                if ((rc = table(pl.cfg.bluestein, &pl.tw_stages, true)) != CROFT_SUCCESS) return rc;
-                if ((rc = blue(pl.n, pl.cfg.bluestein, &pl)) != CROFT_SUCCESS) return rc;
+                const int m = pl.cfg.bluestein;
+                if ((rc = stages(m)) != CROFT_SUCCESS) return rc;
+                if (!at.count({2, pl.n})) {
+                    std::vector<double> c(2 * (size_t)pl.n), b(2 * (size_t)m);
+                    bluestein_tables_fp64(pl.n, m, c.data(), b.data());
+                    append(2, pl.n, c);
+                    append(3, pl.n, b);
+                }
             } else if (pl.n > 1) {
-                // both where the autotuner may change the kernel, and for the
-                // batched kernel, which reads the first
-                const bool measure = (p->flags & CROFT_MEASURE) != 0;
-                if ((!pl.cfg.stage_table || measure || p->batched) && (rc = table(pl.n, &pl.tw)) != CROFT_SUCCESS)
-                    return rc;
-                if ((pl.cfg.stage_table || (measure && !pl.cfg.generic)) &&
-                    (rc = table(pl.n, &pl.tw_stages, true)) != CROFT_SUCCESS)
+                // both orders where the autotuner may change the kernel; the
+                // batched kernel reads the natural one
+                if (!pl.cfg.stage_table || measure || p->batched) twiddles(pl.n);
+                if ((pl.cfg.stage_table || (measure && !pl.cfg.generic)) && (rc = stages(pl.n)) != CROFT_SUCCESS)
                     return rc;
             }
-            if (pl.kind == kRealX && (rc = table(2 * pl.n, &pl.tw2)) != CROFT_SUCCESS) return rc;
+            if (pl.kind == kRealX) twiddles(2 * pl.n);
             if ((rc = prepare_kernel(&pl.cfg)) != CROFT_SUCCESS) return rc;
         }
     }
+    if (!host.empty()) {
+        if ((e = plan_alloc(p, &p->tables, host.size())) != hipSuccess) {
+            (void)hipGetLastError();
+            p->tables = nullptr;
+            return fail(CROFT_ERR_OUT_OF_MEMORY, "twiddle tables: %s", hipGetErrorString(e));
+        }
+        if ((e = hipMemcpy(p->tables, host.data(), host.size(), hipMemcpyHostToDevice)) != hipSuccess)
+            return fail_hip(e, "twiddle upload");
+    }
+    auto where = [&](int kind, int n) -> const void * {
+        const auto it = at.find({kind, n});
+        return it == at.end() ? nullptr : static_cast<const char *>(p->tables) + it->second;
+    };
+    for (auto &ps : p->passes)
+        for (PassLaunch &pl : ps) {
+            pl.tw = where(0, pl.n);
+            pl.tw_stages = where(1, pl.cfg.bluestein ? pl.cfg.bluestein : pl.n);
+            if (pl.kind == kRealX) pl.tw2 = where(0, 2 * pl.n);
+            pl.chirp = where(2, pl.n);
+            pl.bhat = where(3, pl.n);
+        }
     if (p->conv) {
         long long count = 1;
         for (const PassLaunch &pl : p->passes[0])

@@ -128,32 +128,7 @@ __global__ void __launch_bounds__(Cfg::kBlock, 2) fft_bluestein(const PassArgs a
             }
         }
     if constexpr (K > 1) {
-        // element t + b T + m NBK to the thread whose first group reads it
-        constexpr int kParts = Cfg::kSplit ? 2 : 1;
-#pragma unroll
-        for (int part = 0; part < kParts; ++part) {
-            stage_sync<Cfg::kWaveSync>();
-#pragma unroll
-            for (int i = 0; i < BK * GK; ++i) {
-                const int at = KIND == kContiguous ? l * Cfg::kLine + t + (i / GK) * T + (i % GK) * NBK
-                                                   : (t + (i / GK) * T + (i % GK) * NBK) * L + l;
-                if constexpr (Cfg::kSplit) reinterpret_cast<R *>(smem)[at] = part ? y[i].y : y[i].x;
-                else reinterpret_cast<cx<R> *>(smem)[at] = y[i];
-            }
-            stage_sync<Cfg::kWaveSync>();
-#pragma unroll
-            for (int i = 0; i < B0 * G0; ++i) {
-                const int at = KIND == kContiguous ? l * Cfg::kLine + t + (i / G0) * T + (i % G0) * NB0
-                                                   : (t + (i / G0) * T + (i % G0) * NB0) * L + l;
-                if constexpr (Cfg::kSplit) {
-                    const R e = reinterpret_cast<const R *>(smem)[at];
-                    if (part) v[i].y = e;
-                    else v[i].x = e;
-                } else {
-                    v[i] = reinterpret_cast<const cx<R> *>(smem)[at];
-                }
-            }
-        }
+        natural_exchange<Cfg, KIND, R>(smem, l, t, y, v);
     } else {
 #pragma unroll
         for (int i = 0; i < B0 * G0; ++i) v[i] = y[i];

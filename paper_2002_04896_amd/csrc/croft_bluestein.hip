@@ -50,7 +50,7 @@ BluesteinLaunch launch_of() {
     // FP64 convolutions stop at 4096 points (lengths up to 2048)
     if constexpr (CB == 8 || M <= 4096) {
         using S = BlueShape<M, KIND, CB>;
-        using Cfg = GCfg<M, KIND, S::L, S::E, CB, S::kSplit, 0, 0, S::T>;
+        using Cfg = GCfg<M, KIND, S::L, S::E, CB, S::kSplit, 0, S::T>;
         static_assert(Cfg::kBlock <= 256 && BlueLds<Cfg, S::kTab>::kBytes <= 160 * 1024, "launch shape");
         b.func = reinterpret_cast<const void *>(&fft_bluestein<Cfg, St, KIND, S::kTab>);
         b.T = Cfg::T;

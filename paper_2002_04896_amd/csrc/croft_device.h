@@ -384,7 +384,8 @@ struct PassArgs {
     const void *chirp;
     const void *bhat;
     int m;
-    int inverse;       // runtime-radix kernel only (static kernels take it as a template argument)
+    int inverse;       // runtime-radix and grouped kernels (static kernels take it as a template argument)
+    int xcd_order;     // grouped kernels, strided: tiles in the XCD-contiguous order
     // runtime-radix kernel only
     int n, T, L, S;
     int radix[kMaxStages];

@@ -10,14 +10,15 @@ namespace dev {
 
 #define DEF(N) make_entry<N, kContiguous, StC128, 16, kC128>(0), make_entry<N, kStrided, StC128, 16, kC128>(0), make_real_entry<N, StC128, 16, kC128>(), \
                make_conv_entry<N, StC128, 16, kC128>(0)
-// lengths whose strided pass is in croft_group_c128.hip
-#define DEFX(N) make_entry<N, kContiguous, StC128, 16, kC128>(0), make_real_entry<N, StC128, 16, kC128>(), \
-                make_conv_entry<N, StC128, 16, kC128>(0)
+// lengths whose fused multiply pass is in croft_group_conv.hip (DEFN), and whose strided pass too
+// is in croft_group_c128.hip (DEFX)
+#define DEFX(N) make_entry<N, kContiguous, StC128, 16, kC128>(0), make_real_entry<N, StC128, 16, kC128>()
+#define DEFN(N) make_entry<N, kStrided, StC128, 16, kC128>(0), DEFX(N)
 // contiguous: 1 padded LDS lines, 2 no prefetch;
 // strided: 1 no prefetch, 2 wide tile (EW elements per thread, LW lines), 3 wide tile with prefetch,
 // 4 wide tile with fewer threads (EW2 elements per thread, LW2 lines),
 // 5 wide tile with non-temporal loads and stores; contiguous 3: non-temporal;
-// fused multiply pass: 0 default shape, 1 wide tile (EW, LW); strided 512: 6, 7, 8 are 1, 2, 4
+// fused multiply pass: 0 default shape, 1 wide tile (EW, LW), 2 in croft_group_conv.hip; strided 512: 6, 7, 8 are 1, 2, 4
 // with each XCD taking a contiguous run of tiles, 9 and 10 are 4 and 8 with non-temporal loads
 // and stores
 #define CAND(N, EW, LW, EW2, LW2)                                                \
@@ -38,8 +39,8 @@ std::vector<Entry> entries_c128() {
     return {
         DEF(2),   DEF(4),   DEF(8),   DEF(16),   DEF(32),   DEF(64),   DEF(128),
         DEF(256), DEF(512), DEF(1024), DEF(2048), DEF(4096), DEF(48),  DEF(60),
-        DEF(72),  DEF(80),  DEF(96),  DEF(100), DEFX(384), DEF(120), DEF(160),
-        DEF(192), DEF(240), DEFX(320), DEFX(480), DEF(200), DEFX(288), DEFX(360),
+        DEFN(72),  DEFN(80),  DEFN(96),  DEFN(100), DEFX(384), DEFN(120), DEFN(160),
+        DEFN(192), DEFN(240), DEFX(320), DEFX(480), DEFN(200), DEFX(288), DEFX(360),
         DEFX(400), DEFX(576), DEFX(640), DEFX(720), DEFX(768), DEFX(960),
         CAND(128, 8, 16, 16, 16), CAND(256, 8, 16, 16, 16), CAND(512, 8, 16, 16, 16), CAND(1024, 16, 8, 32, 8),
         make_entry<512, kStrided, StC128, 16, kC128, 0, 0, 0, 0, 0, 1>(6),

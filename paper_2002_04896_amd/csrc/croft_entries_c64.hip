@@ -10,9 +10,11 @@ namespace dev {
 
 #define DEF(N) make_entry<N, kContiguous, StC64, 8, kC64>(0), make_entry<N, kStrided, StC64, 8, kC64>(0), make_real_entry<N, StC64, 8, kC64>(), \
                make_conv_entry<N, StC64, 8, kC64>(0)
-// lengths whose strided pass (DEFX) and contiguous pass too (DEFR) are in croft_group_c64.hip
-#define DEFR(N) make_real_entry<N, StC64, 8, kC64>(), make_conv_entry<N, StC64, 8, kC64>(0)
+// lengths whose fused multiply pass is in croft_group_conv.hip (DEFN), and whose strided pass (DEFX)
+// and contiguous pass too (DEFR) are in croft_group_c64.hip
+#define DEFR(N) make_real_entry<N, StC64, 8, kC64>()
 #define DEFX(N) make_entry<N, kContiguous, StC64, 8, kC64>(0), DEFR(N)
+#define DEFN(N) make_entry<N, kStrided, StC64, 8, kC64>(0), DEFX(N)
 // contiguous: 1 padded LDS lines, 2 no prefetch;
 // strided: 1 no prefetch, 2 wide tile (EW elements per thread, LW lines), 3 wide tile with prefetch,
 // 4 wide tile with fewer threads (EW2 elements per thread, LW2 lines),
@@ -27,7 +29,7 @@ namespace dev {
 // XCD-contiguous order, 10 to 12 are 6 with that copy (non-temporal stores in 11, loads and stores
 // in 12); contiguous 3:
 // non-temporal;
-// fused multiply pass: 0 default shape, 1 wide tile (EW, LW); strided 384: 6 and 7 are 1 and 0
+// fused multiply pass: 0 default shape, 1 wide tile (EW, LW), more in croft_group_conv.hip; strided 384: 6 and 7 are 1 and 0
 // (without and with prefetch) in the XCD-contiguous tile order, 8 is in croft_group_c64.hip
 #define CAND(N, EW, LW, EW2, LW2)                                                \
     make_entry<N, kContiguous, StC64, 8, kC64, 0, 0, 1, 1>(1),                 \
@@ -44,8 +46,8 @@ std::vector<Entry> entries_c64() {
     return {
         DEF(2),   DEF(4),   DEF(8),   DEF(16),   DEF(32),   DEF(64),   DEF(128),
         DEF(256), DEF(512), DEF(1024), DEF(2048), DEF(4096), DEF(48),  DEF(60),
-        DEF(72),  DEF(80),  DEF(96),  DEF(100), DEF(384), DEF(120), DEF(160),
-        DEF(192), DEF(240), DEFX(320), DEFX(480), DEF(200), DEFX(288), DEFX(360),
+        DEFN(72),  DEFN(80),  DEFN(96),  DEFN(100), DEF(384), DEFN(120), DEFN(160),
+        DEFN(192), DEFN(240), DEFX(320), DEFX(480), DEFN(200), DEFX(288), DEFX(360),
         DEFX(400), DEFR(576), DEFR(640), DEFR(720), DEFR(768), DEFR(960),
         CAND(128, 16, 32, 32, 32), CAND(256, 16, 32, 32, 32), CAND(512, 16, 32, 32, 32), CAND(1024, 32, 16, 64, 16),
         make_lanes_entry<512, StC64, kC64, 0>(6), with_plain(make_lanes_entry<512, StC64, kC64, 3>(7), 6),

@@ -83,11 +83,9 @@ constexpr GroupPlan make_groups(const RPlan &p, int emax) {
 // Launch shape: L lines per block, T threads per line, at most EMAX elements
 // held by a thread.  One block per tile (the kernel does not loop): several
 // small blocks on a CU overlap one tile's loads with another's stages.
-template <int N, int KIND, int LREQ, int EMAX, int COMPUTE_BYTES, int SPLIT, int XO = 0, int NT = 0,
-          int TREQ = 0>
+template <int N, int KIND, int LREQ, int EMAX, int COMPUTE_BYTES, int SPLIT, int NT = 0, int TREQ = 0>
 struct GCfg {
     static constexpr int kCB = COMPUTE_BYTES;
-    static constexpr bool kXO = XO != 0;
     static constexpr bool kNT = NT != 0;
     static constexpr RPlan plan = make_rplan(N);
     static constexpr GroupPlan groups = make_groups(plan, EMAX);
@@ -237,6 +235,50 @@ __device__ __forceinline__ void run_groups(unsigned char *smem, const cx<R> *tws
     }
 }
 
+// A line in natural order across its threads (element t + b T + m N/GK of the
+// last group's outputs in y[b GK + m]) to the inputs of the first group,
+// v[b G0 + m] = element t + b T + m N/G0.
+template <class Cfg, int KIND, typename R>
+__device__ __forceinline__ void natural_exchange(unsigned char *smem, int l, int t, const cx<R> *y, cx<R> *v) {
+    constexpr int N = Cfg::plan.n, T = Cfg::T, K = Cfg::groups.K;
+    constexpr int G0 = Cfg::size(0), NB0 = N / G0, B0 = (NB0 + T - 1) / T;
+    constexpr int GK = Cfg::size(K - 1), NBK = N / GK, BK = (NBK + T - 1) / T;
+    constexpr int kParts = Cfg::kSplit ? 2 : 1;
+    static_assert(K > 1, "one group holds the whole line");
+#pragma unroll
+    for (int part = 0; part < kParts; ++part) {
+        stage_sync<Cfg::kWaveSync>();
+#pragma unroll
+        for (int b = 0; b < BK; ++b) {
+            if ((NBK % T) == 0 || t + b * T < NBK) {
+#pragma unroll
+                for (int m = 0; m < GK; ++m) {
+                    const int i = group_lds<Cfg, KIND>(l, t + b * T + m * NBK);
+                    if constexpr (Cfg::kSplit) reinterpret_cast<R *>(smem)[i] = part ? y[b * GK + m].y : y[b * GK + m].x;
+                    else reinterpret_cast<cx<R> *>(smem)[i] = y[b * GK + m];
+                }
+            }
+        }
+        stage_sync<Cfg::kWaveSync>();
+#pragma unroll
+        for (int b = 0; b < B0; ++b) {
+            if ((NB0 % T) == 0 || t + b * T < NB0) {
+#pragma unroll
+                for (int m = 0; m < G0; ++m) {
+                    const int i = group_lds<Cfg, KIND>(l, t + b * T + m * NB0);
+                    if constexpr (Cfg::kSplit) {
+                        const R e = reinterpret_cast<const R *>(smem)[i];
+                        if (part) v[b * G0 + m].y = e;
+                        else v[b * G0 + m].x = e;
+                    } else {
+                        v[b * G0 + m] = reinterpret_cast<const cx<R> *>(smem)[i];
+                    }
+                }
+            }
+        }
+    }
+}
+
 // One kernel serves both directions (swap(DFT(swap x)) by a uniform flag: two
 // selects per access in a pass that waits for memory).
 template <class Cfg, class St, int KIND>
@@ -254,7 +296,7 @@ __global__ void __launch_bounds__(Cfg::kBlock) fft_group(const PassArgs a) {
     const int l = KIND == kContiguous ? tid / T : tid % L;
     const int t = KIND == kContiguous ? tid % T : tid / L;
     const long long es = KIND == kContiguous ? 1 : a.es;
-    const long long tile = Cfg::kXO ? xcd_tile(blockIdx.x, gridDim.x) : (long long)blockIdx.x;
+    const long long tile = a.xcd_order ? xcd_tile(blockIdx.x, gridDim.x) : (long long)blockIdx.x;
     const long long tx = KIND == kContiguous ? tile : tile % a.ntiles;
     const long long w = KIND == kContiguous ? 0 : tile / a.ntiles;
     const long long q = tx * L + l;
@@ -347,6 +389,123 @@ __global__ void __launch_bounds__(Cfg::kBlock) fft_group(const PassArgs a) {
     }
 }
 
+// The fused forward FFT / multiply / inverse FFT pass of a convolution plan
+// (fft_conv_z: the same product, weights and energy terms) on the grouped
+// stages: the product happens on the registers the forward FFT leaves, which
+// one exchange brings to the inverse FFT's first group.  One block per tile,
+// one energy partial per block, summed over the block in a fixed order.
+template <class Cfg, class St>
+__global__ void __launch_bounds__(Cfg::kBlock) fft_group_conv(const PassArgs a) {
+    using R = typename St::R;
+    using Raw = typename St::Raw;
+    extern __shared__ __align__(16) unsigned char smem[];
+    constexpr int N = Cfg::plan.n, T = Cfg::T, L = Cfg::L, K = Cfg::groups.K;
+    constexpr int G0 = Cfg::size(0), NB0 = N / G0, B0 = (NB0 + T - 1) / T;
+    constexpr int GK = Cfg::size(K - 1), NBK = N / GK, BK = (NBK + T - 1) / T;
+    cx<R> *tws = reinterpret_cast<cx<R> *>(smem + Cfg::kTw);
+    const int tid = threadIdx.x;
+    const int l = tid % L;
+    const int t = tid / L;
+    const long long es = a.es;
+    const long long tile = a.xcd_order ? xcd_tile(blockIdx.x, gridDim.x) : (long long)blockIdx.x;
+    const long long tx = tile % a.ntiles, w = tile / a.ntiles;
+    const long long q = tx * L + l;
+    const bool valid = q < es;
+    const long long tbase = tx * L + w * es * N;
+    const unsigned lane = (unsigned)(((long long)l + (long long)t * es) * (long long)sizeof(Raw));
+    const unsigned glane = lane / 2;  // the multiplier: one real per element
+    // the line and its multiplier, every load of the thread in flight
+    Raw raw[B0 * G0];
+    R g[BK * GK];
+    if (valid) {
+        gchar *const ib = uniform_gptr(a.in, tbase * (long long)sizeof(Raw));
+        gchar *const gb = uniform_gptr(a.mul, tbase * (long long)sizeof(R));
+#pragma unroll
+        for (int b = 0; b < B0; ++b) {
+            if ((NB0 % T) == 0 || t + b * T < NB0) {
+                const unsigned lr = lane_reg(lane);
+#pragma unroll
+                for (int m = 0; m < G0; ++m)
+                    raw[b * G0 + m] = fetch_at<St, false, false>(ib, (long long)(b * T + m * NB0) * es, lr);
+            }
+        }
+#pragma unroll
+        for (int b = 0; b < BK; ++b) {
+            if ((NBK % T) == 0 || t + b * T < NBK) {
+                const unsigned lr = lane_reg(glane);
+#pragma unroll
+                for (int m = 0; m < GK; ++m)
+                    g[b * GK + m] = *(const __attribute__((address_space(1))) R *)(
+                        gb + (long long)(b * T + m * NBK) * es * (long long)sizeof(R) + lr);
+            }
+        }
+    }
+    {
+        const cx<R> *W = reinterpret_cast<const cx<R> *>(a.tw);
+        for (int i = tid; i < Cfg::kTwN; i += Cfg::kBlock) tws[i] = W[i];
+        __syncthreads();
+    }
+    cx<R> v[B0 * G0], y[BK * GK];
+#pragma unroll
+    for (int i = 0; i < B0 * G0; ++i) v[i] = St::decode(raw[i], 0);
+    run_groups<Cfg, kStrided, 0, R>(smem, tws, l, t, v, y);
+    double acc = 0.0;
+    if (valid) {
+        const long long kx = q % a.hx;
+        const double wgt = (kx == 0 || kx == a.hx - 1) ? 1.0 : 2.0;
+#pragma unroll
+        for (int b = 0; b < BK; ++b) {
+            if ((NBK % T) == 0 || t + b * T < NBK) {
+#pragma unroll
+                for (int m = 0; m < GK; ++m) {
+                    cx<R> &o = y[b * GK + m];
+                    const R gv = g[b * GK + m];
+                    const double m2 = (double)o.x * o.x + (double)o.y * o.y;
+                    acc = fma(wgt * (double)gv, m2, acc);
+                    o = cx<R>{o.y * gv, o.x * gv};  // the product, swapped for the inverse
+                }
+            }
+        }
+    }
+    natural_exchange<Cfg, kStrided, R>(smem, l, t, y, v);
+    run_groups<Cfg, kStrided, 0, R>(smem, tws + opaque_zero(), l, t, v, y);
+    if (valid) {
+        gchar *const ob = uniform_gptr(a.out, tbase * (long long)sizeof(Raw));
+#pragma unroll
+        for (int b = 0; b < BK; ++b) {
+            if ((NBK % T) == 0 || t + b * T < NBK) {
+                const unsigned lr = lane_reg(lane);
+#pragma unroll
+                for (int m = 0; m < GK; ++m)
+                    store_at<St, false, false>(ob, (long long)(b * T + m * NBK) * es, lr,
+                                               cx<R>{y[b * GK + m].y, y[b * GK + m].x}, 0);
+            }
+        }
+    }
+    // the block's sum: a butterfly over each wavefront, then its wavefronts in order
+#pragma unroll
+    for (int h = 32; h > 0; h /= 2) acc += __shfl_xor(acc, h, 64);
+    double *sum = reinterpret_cast<double *>(smem);
+    __syncthreads();  // the exchange area is free
+    if ((tid & 63) == 0) sum[tid >> 6] = acc;
+    __syncthreads();
+    if (tid == 0) {
+        double s = sum[0];
+        for (int i = 1; i < (Cfg::kBlock + 63) / 64; ++i) s += sum[i];
+        a.partial[blockIdx.x] = s;
+    }
+}
+
+// Elements a thread holds at short lengths (FP32 and FP64): 10, or the largest
+// radix, or 16 where that saves a trip through LDS.  Few registers let more
+// blocks share a CU (complex64 fused pass at 150 points, 16 / 10 elements:
+// 28 / 25 us, 200 39 / 34; 180, where 16 saves a trip, 27 / 32).
+constexpr int short_elements(int n) {
+    const RPlan p = make_rplan(n);
+    const int e = p.rmax > 10 ? p.rmax : 10;
+    return e < 16 && make_groups(p, 16).K < make_groups(p, e).K ? 16 : e;
+}
+
 // The shape of a pass by length and storage.  What bounds these passes is how
 // many loads a CU keeps in flight and the LDS trips between them, so the rule
 // takes rows of one 128-byte line (64 bytes for 16-bit storage above 480,
@@ -370,8 +529,9 @@ struct GroupShape {
     // contiguous 16-bit storage above 256: 32 elements where that takes two
     // trips (400 205 -> 182 us), else 16 (960 284 -> 198)
     static constexpr int E = !kStridedPass ? (STORE_BYTES == 4 && N > 256 && make_groups(make_rplan(N), 32).K <= 2 ? 32 : 16)
-                             : STORE_BYTES == 16 ? 20
                              : STORE_BYTES == 4  ? (N <= 180 ? 16 : 32)
+                             : N <= 256          ? short_elements(N)
+                             : STORE_BYTES == 16 ? 20
                              : N == 960          ? 64
                              : (N == 576 || N == 640 || N >= 900) ? 48
                                                                   : 32;
@@ -382,10 +542,7 @@ template <int N, class St, int SB, int DT, int KIND, int NT = 0>
 Entry make_group_entry(int cand) {
     constexpr int CB = (int)sizeof(cx<typename St::R>);
     using S = GroupShape<N, KIND, SB, CB>;
-    // strided tiles in the XCD-contiguous order: rows that are not whole
-    // 128-byte lines share them with the next tile (complex64 at 400, rows of
-    // 360 elements: 183 -> 168 us; of 36000 elements 146 -> 147)
-    using Cfg = GCfg<N, KIND, S::L, S::E, CB, S::kSplit, KIND == kStrided ? 1 : 0, NT>;
+    using Cfg = GCfg<N, KIND, S::L, S::E, CB, S::kSplit, NT>;
     static_assert(Cfg::kBlock <= 1024, "block too large");
     static_assert(Cfg::kLds <= 160 * 1024, "LDS beyond the 160 KiB of a gfx950 workgroup");
     Entry e;
@@ -403,10 +560,37 @@ Entry make_group_entry(int cand) {
     return e;
 }
 
+// The fused multiply pass of length N in tiles of L lines, at most E elements
+// held by a thread.
+template <int N, class St, int SB, int DT, int L, int E>
+Entry make_group_conv_entry(int cand) {
+    constexpr int CB = (int)sizeof(cx<typename St::R>);
+    using Cfg = GCfg<N, kStrided, L, E, CB, ((long long)N * L * CB > 48 * 1024 ? 1 : 0)>;
+    static_assert(Cfg::kBlock <= 1024, "block too large");
+    static_assert(Cfg::kLds <= 160 * 1024, "LDS beyond the 160 KiB of a gfx950 workgroup");
+    static_assert(Cfg::kX >= 16 * sizeof(double), "wavefront sums fit the exchange area");
+    Entry e;
+    e.n = N;
+    e.kind = kConvZ;
+    e.dtype = DT;
+    e.cand = cand;
+    e.func[0] = e.func[1] = reinterpret_cast<const void *>(&fft_group_conv<Cfg, St>);
+    e.T = Cfg::T;
+    e.L = Cfg::L;
+    e.block = Cfg::kBlock;
+    e.lds = Cfg::kLds;
+    e.plan = Cfg::plan;
+    e.one_tile = true;
+    return e;
+}
+
 // The 2^a 3^b 5^c lengths up to 1024 that fft_group runs as strided passes,
-// for every storage (long lines), and for 16-bit storage also the short ones
-// (FP32 storage keeps fft_static there: 150 151/149 us against 173/159, 25
-// 154/132 against 148/147).
+// for every storage (long lines), and for 16-bit storage also the short ones.
+// FP32 and FP64 storage keep fft_static there where rows are whole 128-byte
+// lines (complex64, 150 points, rows of 360 and 36000: 151/149 us against
+// 173/159) and take fft_group, in its tile order, where they are not
+// (CROFT_GROUP_PARTIAL: 97 elements a row, 25 MB: 162 points 18.6 -> 10.3 us,
+// 240 22.8 -> 13.7; complex128 180 28.4 -> 17.9).
 #define CROFT_GROUP_LONG(X)                                                                                        \
     X(243) X(250) X(270) X(288) X(300) X(320) X(324) X(360) X(375) X(400) X(405) X(432) X(450) X(480) X(486) X(500) \
     X(540) X(576) X(600) X(625) X(640) X(648) X(675) X(720) X(729) X(750) X(768) X(800) X(810) X(864) X(900) X(960) \
@@ -414,6 +598,10 @@ Entry make_group_entry(int cand) {
 #define CROFT_GROUP_SHORT(X)                                                                                       \
     X(18) X(20) X(24) X(25) X(27) X(30) X(36) X(40) X(45) X(50) X(54) X(75) X(81) X(90) X(108) X(125) X(135)         \
     X(144) X(150) X(162) X(180) X(216) X(225)
+
+#define CROFT_GROUP_PARTIAL(X)                                                                                     \
+    X(48) X(54) X(60) X(64) X(72) X(75) X(80) X(81) X(90) X(96) X(100) X(108) X(120) X(125) X(135) X(144) X(150)     \
+    X(160) X(162) X(180) X(192) X(200) X(216) X(225) X(240)
 
 }  // namespace dev
 }  // namespace croft

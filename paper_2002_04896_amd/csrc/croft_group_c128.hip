@@ -9,6 +9,8 @@ namespace dev {
 // (0.8 GB moved: 400 149 us against 151, 864 148 against 144, 1000 142
 // against 189)
 #define STRIDED(N) make_group_entry<N, StC128, 16, kC128, kStrided>(0),
+// beside the stage-by-stage tile (candidate 0): taken where rows are not whole 128-byte lines
+#define PARTIAL(N) make_group_entry<N, StC128, 16, kC128, kStrided>(1),
 #define SHORT(N) make_entry<N, kStrided, StC128, 16, kC128>(0),
 #define LINES(N) make_entry<N, kContiguous, StC128, 16, kC128>(0),
 
@@ -17,6 +19,9 @@ std::vector<Entry> group_entries_c128() {
         CROFT_GROUP_LONG(STRIDED)
         make_group_entry<384, StC128, 16, kC128, kStrided>(0),
         CROFT_GROUP_SHORT(SHORT)
+        CROFT_GROUP_PARTIAL(PARTIAL)
+        // the same at 128 and 256: 6, beside the candidates of croft_entries_c128.hip
+        make_group_entry<128, StC128, 16, kC128, kStrided>(6), make_group_entry<256, StC128, 16, kC128, kStrided>(6),
         LINES(75) LINES(81) LINES(90) LINES(108) LINES(125) LINES(135) LINES(144) LINES(150) LINES(162) LINES(180)
         LINES(216) LINES(225) LINES(243) LINES(250) LINES(270) LINES(300) LINES(324) LINES(375) LINES(405) LINES(432)
         LINES(450) LINES(486) LINES(500) LINES(540) LINES(600) LINES(625) LINES(648) LINES(675) LINES(729) LINES(750)

@@ -10,6 +10,8 @@ namespace dev {
 // are as fast or faster.  Contiguous lines shorter than 75 and strided ones
 // shorter than 18 stay on the runtime-radix kernel.
 #define STRIDED(N) make_group_entry<N, StC64, 8, kC64, kStrided>(0),
+// beside the stage-by-stage tile (candidate 0): taken where rows are not whole 128-byte lines
+#define PARTIAL(N) make_group_entry<N, StC64, 8, kC64, kStrided>(1),
 #define SHORT(N) make_entry<N, kStrided, StC64, 8, kC64>(0),
 #define LINES(N) make_entry<N, kContiguous, StC64, 8, kC64>(0),
 #define GLINES(N) make_group_entry<N, StC64, 8, kC64, kContiguous>(0),
@@ -22,6 +24,9 @@ std::vector<Entry> group_entries_c64() {
         // 384: 8, beside the candidates of croft_entries_c64.hip (174/136 us against 182/148)
         make_group_entry<384, StC64, 8, kC64, kStrided>(8),
         CROFT_GROUP_SHORT(SHORT)
+        CROFT_GROUP_PARTIAL(PARTIAL)
+        // the same at 128 and 256: 6, beside the candidates of croft_entries_c64.hip
+        make_group_entry<128, StC64, 8, kC64, kStrided>(6), make_group_entry<256, StC64, 8, kC64, kStrided>(6),
         LINES(75) LINES(81) LINES(90) LINES(108) LINES(125) LINES(135) LINES(144) LINES(150) LINES(162) LINES(180)
         LINES(216) LINES(225) LINES(243) LINES(250) LINES(270) LINES(300) LINES(324) LINES(375) LINES(405) LINES(432)
         LINES(450)

@@ -113,6 +113,8 @@ struct Geometry {
 // ---- kernels (croft_kernels.hip) ----
 // Number of compiled static configurations for (n, kind, dtype).
 int kernel_candidates(int n, int kind, int dtype);
+// The candidate of a strided pass that runs the grouped stages, -1 if none.
+int grouped_candidate(int n, int dtype);
 // Look up compiled configuration `cand` (0 = default; an unknown index falls
 // back to 0) for a pass; with force_generic, or when no static kernel exists,
 // the runtime-radix kernel.  Returns false if no kernel can run it.
@@ -187,6 +189,12 @@ hipError_t noalloc_scratch(int device, int8_t **ptr);
 // strided pass (a choice for that axis first, then one for any axis), -1
 // for the other kinds.
 bool wisdom_lookup(int n, int kind, int dtype, int dir, int axis, int *cand, int *waves);
+// The part of it that was measured for this process or its CROFT_WISDOM file
+// (no built-in choice).
+bool wisdom_measured(int n, int kind, int dtype, int axis, int *cand, int *waves);
+// The choice for a fused multiply pass that wisdom_lookup has none for.
+// partial_lines: its rows are not whole 128-byte lines.
+void conv_choice(int n, int dtype, long long spectrum_bytes, bool partial_lines, int *cand, int *waves);
 void wisdom_record(int n, int kind, int dtype, int axis, int cand, int waves, bool persist);
 // Slab count K of the pipelined schedule for a grid and dtype (K divides nz).
 bool slab_wisdom_lookup(int nx, int ny, int nz, int dtype, int *k);

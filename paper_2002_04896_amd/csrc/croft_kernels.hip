@@ -20,6 +20,8 @@ std::vector<Entry> group_entries_c64();
 std::vector<Entry> group_entries_c128();
 std::vector<Entry> group_entries_c16f();
 std::vector<Entry> group_entries_c16b();
+std::vector<Entry> group_conv_entries_c64();
+std::vector<Entry> group_conv_entries_c128();
 std::vector<Entry> group_entries_c16f_x();
 std::vector<Entry> group_entries_c16b_x();
 }  // namespace dev
@@ -262,7 +264,8 @@ const std::vector<Entry> &table() {
     static const std::vector<Entry> t = [] {
         std::vector<Entry> v;
         for (auto f : {entries_c64, entries_c128, entries_c16f, entries_c16b, group_entries_c64, group_entries_c128,
-                       group_entries_c16f, group_entries_c16b, group_entries_c16f_x, group_entries_c16b_x}) {
+                       group_entries_c16f, group_entries_c16b, group_entries_c16f_x, group_entries_c16b_x,
+                       group_conv_entries_c64, group_conv_entries_c128}) {
             std::vector<Entry> e = f();
             v.insert(v.end(), e.begin(), e.end());
         }
@@ -310,6 +313,12 @@ __global__ void __launch_bounds__(256) sum_partials(const double *partial, int n
 }
 
 }  // namespace
+
+int grouped_candidate(int n, int dtype) {
+    for (const Entry &e : table())
+        if (e.n == n && e.kind == kStrided && e.dtype == dtype && e.one_tile) return e.cand;
+    return -1;
+}
 
 int kernel_candidates(int n, int kind, int dtype) {
     int c = 0;
@@ -426,9 +435,24 @@ long long pass_blocks(const PassLaunch &pl) {
     return blocks;
 }
 
+// The grouped strided kernels deal their tiles to the XCDs in contiguous runs
+// where rows are not whole 128-byte lines: neighbouring tiles share the lines
+// at their edges, which then meet in one L2 (complex64, 180 points, 97
+// elements a row, 25 MB: 15.0 -> 10.1 us, complex128 27.8 -> 17.9; 400 points,
+// 360 a row, 0.8 GB moved: 183 -> 168).  With whole lines the order of
+// dispatch is the faster for FP32 (240 points, 36000 a row: 141 -> 133 us) and
+// as fast for FP64 (the fused pass at 512 points of 257 x 512 lines, 350 ->
+// 299 us); 16-bit storage takes the runs always (250: 202 -> 195), and so do
+// tiles narrower than a line (fused, 1000 points of 257 x 512 lines, 8 lines
+// a tile: 1408 us in dispatch order, 1024 points in runs 707).
+static bool tiles_in_xcd_order(const PassLaunch &pl, int dtype) {
+    if (!strided_kind(pl.kind)) return false;
+    const long long eb = (long long)element_bytes(dtype);
+    return eb == 4 || (pl.es * eb) % 128 != 0 || (pl.cfg.lines * eb) % 128 != 0;
+}
+
 hipError_t launch_pass(const PassLaunch &pl, int dtype, const void *in, void *out, const int8_t *in_exp,
                        int8_t *out_exp, int inverse, hipStream_t stream, const void *mul, double *partial) {
-    (void)dtype;
     PassArgs a;
     a.in = in;
     a.out = out;
@@ -446,6 +470,7 @@ hipError_t launch_pass(const PassLaunch &pl, int dtype, const void *in, void *ou
     a.nw = pl.nw;
     a.em = pl.em;
     a.inverse = inverse;
+    a.xcd_order = tiles_in_xcd_order(pl, dtype);
     a.n = pl.n;
     a.T = pl.cfg.threads_per_line;
     a.L = pl.cfg.lines;

@@ -47,8 +47,8 @@ const Builtin kBuiltin[] = {
     {400, 0, 0, 3, 0}, {480, 0, 0, 3, 0}, {576, 0, 0, 3, 0}, {640, 0, 0, 3, 0}, {720, 0, 0, 3, 0}, {768, 0, 0, 3, 0},
     {960, 0, 0, 3, 0},
     {512, 0, 0, 3, 0}, {512, 1, 0, 4, 4}, {1024, 0, 0, 3, 0}, {1024, 1, 0, 7, 1}, {32, 2, 0, 0, 0},
-    {64, 2, 0, 0, 2}, {64, 3, 0, 0, 2}, {128, 2, 0, 0, 1}, {128, 3, 0, 0, 2}, {256, 2, 0, 1, 0},
-    {256, 3, 0, 0, 1}, {512, 3, 0, 0, 2},
+    {64, 2, 0, 0, 2}, {64, 3, 0, 0, 2}, {128, 2, 0, 0, 1}, {256, 2, 0, 1, 0},
+    
     // complex64 batched tile shapes (kinds 4 and 5: the batched kernel's
     // contiguous and strided passes; candidate = shape), the majority of six
     // CROFT_MEASURE runs (both directions) on the 64-grid PME batch; the
@@ -64,8 +64,8 @@ const Builtin kBuiltin[] = {
     // streaming x tile; 720 keeps the default, which it did not beat
     {400, 0, 1, 3, 0}, {480, 0, 1, 3, 0}, {576, 0, 1, 3, 0}, {640, 0, 1, 3, 0}, {768, 0, 1, 3, 0},
     {512, 0, 1, 3, 0}, {512, 1, 1, 4, 2}, {1024, 0, 1, 2, 0}, {1024, 1, 1, 5, 0}, {32, 2, 1, 0, 2},
-    {64, 2, 1, 0, 1}, {64, 3, 1, 0, 0}, {128, 2, 1, 0, 1}, {128, 3, 1, 1, 1}, {256, 2, 1, 0, 2},
-    {256, 3, 1, 0, 2}, {512, 3, 1, 0, 1},
+    {64, 2, 1, 0, 1}, {64, 3, 1, 0, 0}, {128, 2, 1, 0, 1}, {256, 2, 1, 0, 2},
+    
     // FP16 storage (strided 128 and 256: the grouped stages; 512 x: the
     // non-temporal contiguous tile on four waves of resident blocks, 0.217 ->
     // 0.195 ms in both directions; the same for BF16)
@@ -160,7 +160,7 @@ bool read_file(const char *path, int n, int kind, int dtype, int axis, int *cand
 }
 }  // namespace
 
-bool wisdom_lookup(int n, int kind, int dtype, int dir, int axis, int *cand, int *waves) {
+bool wisdom_measured(int n, int kind, int dtype, int axis, int *cand, int *waves) {
     std::lock_guard<std::mutex> lk(g_mu);
     const char *path = std::getenv("CROFT_WISDOM");
     if (path && *path) {
@@ -176,6 +176,11 @@ bool wisdom_lookup(int n, int kind, int dtype, int dir, int axis, int *cand, int
             return true;
         }
     }
+    return false;
+}
+
+bool wisdom_lookup(int n, int kind, int dtype, int dir, int axis, int *cand, int *waves) {
+    if (wisdom_measured(n, kind, dtype, axis, cand, waves)) return true;
     if (axis >= 0) {
         for (const BuiltinAxis &b : kBuiltinAxis) {
             if (b.n == n && b.kind == kind && b.dtype == dtype && b.axis == axis) {
@@ -214,6 +219,26 @@ void wisdom_record(int n, int kind, int dtype, int axis, int cand, int waves, bo
         else std::fprintf(f, "%d %d %d %d %d\n", n, kind, dtype, cand, waves);
         std::fclose(f);
     }
+}
+
+// The fused multiply pass: the grouped stages at every length that has them
+// (us on a half spectrum of 129 x 256 and of 257 x 512 lines; stage by stage
+// before: complex64 75 14.6, 40 (15.5, 42), 150 25, 88 (30, 101), 200 34, 126
+// (38, 138), 256 39, 142 (42, 147), 360 67, 228 (87, 317), 512 95, 299 (118,
+// 373); complex128 108 32, 126 (38, 142), 180 50, 207 (74, 303), 256 97, 270
+// (93, 303), 512 209, 548 (244, 704)).  Above 256 complex64 has 16- and 8-line
+// tiles: the narrow ones (half a line of memory each, so in XCD order, but
+// more blocks on a CU) where rows share lines anyway and the spectrum stays in
+// the last-level cache (97 x 180 lines: 360 29 against 39, 512 35 against 46;
+// of 211 MB and above they lose, 360 309 against 262; the line is drawn at
+// 64 MiB), and alone above 512 (625 488 against 594).
+void conv_choice(int n, int dtype, long long spectrum_bytes, bool partial_lines, int *cand, int *waves) {
+    const bool narrow = partial_lines && spectrum_bytes <= (64LL << 20);
+    *cand = 0;
+    *waves = 1;  // the stage-by-stage tiles: one wave of resident blocks
+    if (n == 128 || n == 256 || n == 1024 || (n == 512 && dtype == kC128)) *cand = 2;
+    else if (dtype == kC64 && (n == 384 || n == 512)) *cand = narrow ? 3 : 2;
+    else if (dtype == kC64 && n > 256 && n < 512) *cand = narrow ? 1 : 0;
 }
 
 // ---- slab count K of the pipelined schedule ----

@@ -12,6 +12,7 @@ import oracle
 import paper_2002_04896_amd as croft
 from paper_2002_04896_amd import synth
 from gpu_helpers import HALF_KIND, TOL, run_fft, run_half
+from test_gpu_conv import run_conv, unfused
 
 pytestmark = pytest.mark.gpu
 
@@ -93,3 +94,35 @@ def test_longest_strided_convolution(direction):
     x = synth.normal_c((2, 4093, 3), seed=54)
     seen, y, _ = run_fft(x, C64, direction)
     assert oracle.rel_l2(y, oracle.dft3d(seen, direction)) <= TOL[C64]
+
+
+# (nx, ny, nz) with the fused axis nz: stage-by-stage and grouped, 16- and
+# 8-line tiles, one tile and several, ragged rows; the last beyond 96 MiB of
+# spectrum, where the wider tile runs
+@pytest.mark.parametrize("dtype", [C64, C128], ids=["c64", "c128"])
+@pytest.mark.parametrize("dims", [(16, 5, 75), (32, 3, 125), (16, 5, 135), (96, 3, 250), (8, 9, 270), (32, 1, 360),
+                                  (16, 3, 500), (64, 2, 540), (16, 2, 960), (8, 3, 1000), (8, 5, 256), (16, 3, 384),
+                                  (32, 2, 512), (8, 3, 1024)], ids=str)
+def test_fused_multiply_matches_oracle_and_unfused_bits(dims, dtype):
+    nx, ny, nz = dims
+    real = np.float32 if dtype == C64 else np.float64
+    x = synth.normal_c((nz, ny, nx), seed=55).real.astype(real)
+    g = np.abs(synth.normal_c((nz, ny, nx // 2 + 1), seed=56).real).astype(real)
+    got, energy = run_conv(x, g, dtype)
+    ref, ref_e = oracle.convolve_real(x.astype(np.float64), g.astype(np.float64))
+    assert oracle.rel_l2(got, ref) <= TOL[dtype]
+    assert abs(energy - ref_e) <= TOL[dtype] * abs(ref_e)
+    plain, _ = unfused(torch.from_numpy(x).cuda(), torch.from_numpy(g).cuda(), dtype)
+    np.testing.assert_array_equal(got, plain.cpu().numpy())
+
+
+@pytest.mark.parametrize("n", [360, 512])
+def test_fused_multiply_of_a_large_spectrum_equals_unfused_bitwise(n):
+    x = torch.randn((n, 250, 512), dtype=torch.float32, device="cuda")
+    g = torch.rand((n, 250, 257), dtype=torch.float32, device="cuda")
+    out = torch.empty_like(x)
+    plan = croft.croft_plan_create_convolution(512, 250, n, C64)
+    croft.croft_execute_convolution(plan, x, g, out)
+    torch.cuda.synchronize()
+    croft.croft_plan_destroy(plan)
+    assert torch.equal(out, unfused(x, g, C64)[0])
