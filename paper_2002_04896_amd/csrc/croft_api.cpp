@@ -141,6 +141,22 @@ int no_kernel(int n, int dtype) {
 // True where the rows of a strided pass are not whole 128-byte lines.
 bool partial_lines(const PassLaunch &p, int dtype) { return (p.es * (long long)element_bytes(dtype)) % 128 != 0; }
 
+// A built-in non-temporal first pass gives way to the plain tile (padded where
+// there is one, candidate 1) where the grid stays in the 256 MB last-level
+// cache, from which the next pass reads it (us, both directions, non-temporal
+// against plain: complex64 384 x 96 x 100 41.8, 33.1, 512 x 96 x 100 49.9,
+// 42.2, 640 x 200 x 160 206, 181, 512 x 320 x 300 (393 MB) 451, 465; complex128
+// 128^3 39.4, 33.3, 512 x 96 x 100 87, 82, 512 x 200 x 160 (262 MB) 263, 269,
+// 512 x 320 x 300 942, 981).
+constexpr long long kCacheBytes = 256LL << 20;
+constexpr int kStreamingLines = 3;  // its candidate number
+void plain_in_cache(const PassLaunch &p, int dtype, int *cand, int *waves) {
+    if (p.kind != kContiguous || is_half(dtype) || *cand != kStreamingLines) return;
+    if (p.nlines * (long long)p.n * (long long)element_bytes(dtype) > kCacheBytes) return;
+    *cand = 1;
+    *waves = 0;
+}
+
 // The configuration a contiguous or strided pass starts from: a measured
 // choice; for FP32 and FP64 rows that are not whole lines the grouped stages,
 // whose tile order keeps the shared lines in one L2 (croft_group.h has the
@@ -160,6 +176,7 @@ void pass_choice(const PassLaunch &p, int dtype, int dir, int *cand, int *waves)
         }
     }
     wisdom_lookup(p.n, p.kind, dtype, dir, axis, cand, waves);
+    plain_in_cache(p, dtype, cand, waves);
 }
 
 // Non-temporal stores of part of a 128-byte line cost a read-modify-write,
@@ -320,7 +337,9 @@ int build_real_passes(const Geometry &g, int dtype, int dir, int flags, std::vec
     xp.kind = kRealX;
     xp.es = 1;
     xp.nlines = (long long)g.ny * g.nz;
-    int cand = 0, waves = 1;
+    // one block per tile where nothing was measured (complex128 160 x 144 x 150
+    // backward 49.0 -> 43.3 us against one wave of resident blocks)
+    int cand = 0, waves = 0;
     wisdom_lookup(m, kRealX, dtype, tune_dir, -1, &cand, &waves);
     if (!select_kernel(m, kRealX, dtype, false, cand, &xp.cfg))
         return fail(CROFT_ERR_UNSUPPORTED_SIZE, "no real x kernel for nx = %d (half length %d)", g.nx, m);

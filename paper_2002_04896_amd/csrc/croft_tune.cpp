@@ -43,8 +43,11 @@ const Builtin kBuiltin[] = {
     // candidate, forward 0.613 -> 0.587 ms, backward 0.675 -> 0.640, convolution
     // 1.207 -> 1.194)
     // complex64 at the larger compiled 2^a 3^b 5^c lengths: the streaming
-    // contiguous tile for x (strided: the grouped stages, their only candidate)
-    {400, 0, 0, 3, 0}, {480, 0, 0, 3, 0}, {576, 0, 0, 3, 0}, {640, 0, 0, 3, 0}, {720, 0, 0, 3, 0}, {768, 0, 0, 3, 0},
+    // contiguous tile for x (strided: the grouped stages, their only candidate);
+    // 160 to 240 strided: the grouped stages too (200 x 400 x 800 z 666 -> 641
+    // us, 384 x 768 x 192 z 556 -> 545, 240^3 y 120.2 -> 118.4)
+    {160, 1, 0, 1, 0}, {192, 1, 0, 1, 0}, {200, 1, 0, 1, 0}, {240, 1, 0, 1, 0},
+    {480, 0, 0, 3, 0}, {576, 0, 0, 3, 0}, {640, 0, 0, 3, 0}, {720, 0, 0, 3, 0}, {768, 0, 0, 3, 0},
     {960, 0, 0, 3, 0},
     {512, 0, 0, 3, 0}, {512, 1, 0, 4, 4}, {1024, 0, 0, 3, 0}, {1024, 1, 0, 7, 1}, {32, 2, 0, 0, 0},
     {64, 2, 0, 0, 2}, {64, 3, 0, 0, 2}, {128, 2, 0, 0, 1}, {256, 2, 0, 1, 0},
@@ -55,14 +58,15 @@ const Builtin kBuiltin[] = {
     // lengths not listed keep shape 0
     {60, 4, 0, 1, 0}, {60, 5, 0, 1, 0}, {64, 4, 0, 1, 0}, {64, 5, 0, 1, 0}, {72, 4, 0, 1, 0}, {72, 5, 0, 1, 0},
     {80, 4, 0, 1, 0}, {80, 5, 0, 1, 0}, {96, 4, 0, 1, 0}, {96, 5, 0, 1, 0}, {100, 5, 0, 1, 0},
-    // complex128
+    // complex128 (128 x: the padded tile, 128 x 256 x 256 153 -> 138 us against
+    // the non-temporal one)
     {32, 0, 1, 0, 4}, {32, 1, 1, 0, 0}, {48, 0, 1, 0, 2}, {48, 1, 1, 0, 4}, {60, 0, 1, 0, 2}, {60, 1, 1, 0, 2},
     {64, 0, 1, 0, 0}, {64, 1, 1, 0, 4}, {72, 0, 1, 0, 1}, {72, 1, 1, 0, 0}, {80, 0, 1, 0, 1}, {80, 1, 1, 0, 0},
-    {96, 0, 1, 0, 2}, {96, 1, 1, 0, 1}, {100, 0, 1, 0, 4}, {100, 1, 1, 0, 1}, {128, 0, 1, 3, 2},
+    {96, 0, 1, 0, 2}, {96, 1, 1, 0, 1}, {100, 0, 1, 0, 4}, {100, 1, 1, 0, 1}, {128, 0, 1, 1, 0},
     {128, 1, 1, 5, 4}, {256, 0, 1, 3, 0}, {256, 1, 1, 5, 0}, {384, 0, 1, 0, 0},
     // complex128 at the larger compiled lengths (one forward sweep of n^3): the
     // streaming x tile; 720 keeps the default, which it did not beat
-    {400, 0, 1, 3, 0}, {480, 0, 1, 3, 0}, {576, 0, 1, 3, 0}, {640, 0, 1, 3, 0}, {768, 0, 1, 3, 0},
+    {480, 0, 1, 3, 0}, {576, 0, 1, 3, 0}, {640, 0, 1, 3, 0}, {768, 0, 1, 3, 0},
     {512, 0, 1, 3, 0}, {512, 1, 1, 4, 2}, {1024, 0, 1, 2, 0}, {1024, 1, 1, 5, 0}, {32, 2, 1, 0, 2},
     {64, 2, 1, 0, 1}, {64, 3, 1, 0, 0}, {128, 2, 1, 0, 1}, {256, 2, 1, 0, 2},
     
@@ -100,6 +104,21 @@ struct BuiltinAxis {
     int n, kind, dtype, axis, cand, waves;
 };
 const BuiltinAxis kBuiltinAxis[] = {
+    // 128 and 256, from sweeps of the whole transform over cubes and flat and
+    // long grids (both directions; us, the choice for any axis before).  The
+    // non-temporal hint pays in the pass along z, which nothing follows, and
+    // costs in the passes before it, whose output the next one reads: complex64
+    // 256^3 z 133 -> 125, 512 x 512 x 256 z 613 -> 541, 512 x 256 x 512 y 570
+    // -> 559, 256 x 128 x 256 y 75.3 -> 69.3; complex128 128^3 y 39.5 -> 35.3,
+    // 256^3 y 296 -> 259 (512 x 256 x 512 1166 -> 1180, 256 x 256 x 1024 1283
+    // -> 1243)
+    {128, 1, 0, 1, 1, 1},
+    {128, 1, 0, 2, 5, 0},
+    {256, 1, 0, 1, 2, 0},
+    {256, 1, 0, 2, 5, 0},
+    {128, 1, 1, 1, 2, 1},
+    {128, 1, 1, 2, 5, 0},
+    {256, 1, 1, 1, 4, 0},
     // complex64 at 1024, 512-thread blocks, one block per tile: y in the
     // XCD-contiguous order (3.40 -> 3.29 ms), z non-temporal (4.16 -> 3.97)
     {1024, 1, 0, 1, 8, 0},
