@@ -828,6 +828,39 @@ __device__ __forceinline__ int tw_source(int i) {
     return src;
 }
 
+// A kernel's LDS tables (twiddles), copied in two halves: fetch() issues the
+// global loads into registers, before the block's first tile is loaded, and
+// store() writes them to LDS, after; the tile's loads are then in flight while
+// the table arrives, instead of waiting for it and a barrier.  A barrier must
+// follow store().  (Longer tables are copied by store() alone.)  Used by the
+// batched tiles, which run once per block: 64 mixed complex64 grids 336 -> 331
+// us.  In fft_static and the real x pass the registers it holds cost more than
+// it hides (complex128 128^3 31 -> 34 us, real 160 x 144 x 150 43 -> 46).
+template <int COUNT, int BLOCK, typename R>
+struct TableCopy {
+    static constexpr int kIter = (COUNT + BLOCK - 1) / BLOCK;
+    static constexpr bool kEarly = kIter <= 4;
+    cx<R> v[kEarly && kIter > 0 ? kIter : 1];
+    template <class Src>
+    __device__ __forceinline__ void fetch(const cx<R> *W, int tid, Src src) {
+        if constexpr (kEarly) {
+#pragma unroll
+            for (int i = 0; i < kIter; ++i)
+                if (COUNT % BLOCK == 0 || tid + i * BLOCK < COUNT) v[i] = W[src(tid + i * BLOCK)];
+        }
+    }
+    template <class Src>
+    __device__ __forceinline__ void store(cx<R> *lds, const cx<R> *W, int tid, Src src) const {
+        if constexpr (kEarly) {
+#pragma unroll
+            for (int i = 0; i < kIter; ++i)
+                if (COUNT % BLOCK == 0 || tid + i * BLOCK < COUNT) lds[tid + i * BLOCK] = v[i];
+        } else {
+            for (int i = tid; i < COUNT; i += BLOCK) lds[i] = W[src(i)];
+        }
+    }
+};
+
 // With one block per tile, workgroup b runs on XCD b mod 8 (the dispatcher
 // deals workgroups to the 8 XCDs in turn); this order gives each XCD one
 // contiguous run of tiles, so its L2 serves neighbouring row segments (a
@@ -1641,11 +1674,10 @@ __device__ __forceinline__ void batch_tile(const PassArgs &a, long long tile, un
     // with whole wavefronts of lines, t is the wavefront's index: uniform
     const int t = KIND == kContiguous ? tid % T
                   : (L % 64 == 0 ? (int)__builtin_amdgcn_readfirstlane((unsigned)(tid / L)) : tid / L);
-    if constexpr (Cfg::kTwN > 0) {
-        const cx<R> *W = reinterpret_cast<const cx<R> *>(a.tw);
-        for (int i = tid; i < Cfg::kTwN; i += Cfg::kBlock) tws[i] = W[tw_source<Cfg>(i)];
-        __syncthreads();
-    }
+    const cx<R> *W = reinterpret_cast<const cx<R> *>(a.tw);
+    auto src = [](int i) { return tw_source<Cfg>(i); };
+    TableCopy<Cfg::kTwN, Cfg::kBlock, R> table;
+    table.fetch(W, tid, src);
     const long long es = KIND == kContiguous ? 1 : a.es;
     const long long tx = KIND == kContiguous ? tile : tile % a.ntiles;
     const long long w = KIND == kContiguous ? 0 : tile / a.ntiles;
@@ -1653,6 +1685,10 @@ __device__ __forceinline__ void batch_tile(const PassArgs &a, long long tile, un
     const unsigned lane = lane_offset<Cfg, St, KIND>(l, t, es);
     Tile<Cfg, St> cur;
     fetch_tile<Cfg, St, KIND, INV>(a, c, t, lane, es, cur);
+    if constexpr (Cfg::kTwN > 0) {
+        table.store(tws, W, tid, src);
+        __syncthreads();
+    }
     int ex = 0;
     static_stage<Cfg, St, KIND, INV, 0>(a, lds, tws, red, t, l, c, lane, es, cur, ex);
 }
