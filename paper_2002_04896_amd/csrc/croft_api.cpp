@@ -164,7 +164,15 @@ void plain_in_cache(const PassLaunch &p, int dtype, int *cand, int *waves) {
 // moved, complex64, against one wave of resident blocks looping over the
 // tiles: strided 25 132 us against 159, 150 149 against 160, 300 contiguous
 // 141 against 164; below 24 MB level).
-void pass_choice(const PassLaunch &p, int dtype, int dir, int *cand, int *waves) {
+// z_first: a z pass that other passes follow (a backward real plan's) takes
+// the built-in choice of the y axis: z's own is for the pass that nothing
+// follows, and its non-temporal stores send the spectrum past the last-level
+// cache, from which the next pass would read it (us, z's choice against y's,
+// complex64 256^3 102.7, 90.9, 512 x 128 x 256 90.4, 79.5, 256 x 512 x 256
+// 215, 186, 512 x 512 x 128 168, 154, 256 x 128 x 512 110, 93.6, 512^3 617,
+// 586, 96 x 96 x 1024 68.1, 66.8; complex128 256^3 212, 185, 256 x 256 x 128
+// 107.6, 93.5).
+void pass_choice(const PassLaunch &p, int dtype, int dir, int *cand, int *waves, bool z_first = false) {
     const int axis = wisdom_axis(p.kind, p.axis);
     *cand = *waves = 0;
     if (wisdom_measured(p.n, p.kind, dtype, axis, cand, waves)) return;
@@ -175,7 +183,7 @@ void pass_choice(const PassLaunch &p, int dtype, int dir, int *cand, int *waves)
             return;
         }
     }
-    wisdom_lookup(p.n, p.kind, dtype, dir, axis, cand, waves);
+    builtin_choice(p.n, p.kind, dtype, dir, z_first && axis == 2 ? 1 : axis, cand, waves);
     plain_in_cache(p, dtype, cand, waves);
 }
 
@@ -355,7 +363,7 @@ int build_real_passes(const Geometry &g, int dtype, int dir, int flags, std::vec
         p.es = axis == 1 ? h : h * g.ny;
         p.nlines = p.es;
         p.nw = axis == 1 ? g.nz : 1;
-        pass_choice(p, dtype, tune_dir, &cand, &waves);
+        pass_choice(p, dtype, tune_dir, &cand, &waves, tune_dir == CROFT_BACKWARD);
         if (!select_kernel(n, kStrided, dtype, (flags & CROFT_FORCE_GENERIC) != 0, cand, &p.cfg))
             return no_kernel(n, dtype);
         if (!lane_offset_fits(p, dtype) && !select_kernel(n, kStrided, dtype, true, 0, &p.cfg))

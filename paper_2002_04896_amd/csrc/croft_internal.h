@@ -189,6 +189,8 @@ hipError_t noalloc_scratch(int device, int8_t **ptr);
 // strided pass (a choice for that axis first, then one for any axis), -1
 // for the other kinds.
 bool wisdom_lookup(int n, int kind, int dtype, int dir, int axis, int *cand, int *waves);
+// Its built-in part alone.
+bool builtin_choice(int n, int kind, int dtype, int dir, int axis, int *cand, int *waves);
 // The part of it that was measured for this process or its CROFT_WISDOM file
 // (no built-in choice).
 bool wisdom_measured(int n, int kind, int dtype, int axis, int *cand, int *waves);

@@ -199,7 +199,11 @@ bool wisdom_measured(int n, int kind, int dtype, int axis, int *cand, int *waves
 }
 
 bool wisdom_lookup(int n, int kind, int dtype, int dir, int axis, int *cand, int *waves) {
-    if (wisdom_measured(n, kind, dtype, axis, cand, waves)) return true;
+    return wisdom_measured(n, kind, dtype, axis, cand, waves) ||
+           builtin_choice(n, kind, dtype, dir, axis, cand, waves);
+}
+
+bool builtin_choice(int n, int kind, int dtype, int dir, int axis, int *cand, int *waves) {
     if (axis >= 0) {
         for (const BuiltinAxis &b : kBuiltinAxis) {
             if (b.n == n && b.kind == kind && b.dtype == dtype && b.axis == axis) {

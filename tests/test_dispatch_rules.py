@@ -48,3 +48,20 @@ def test_a_wisdom_line_comes_before_the_rules(tmp_path, monkeypatch):
 def test_fused_tiles(dims, L):
     p = [q for q in parse_describe(croft.croft_plan_describe_convolution(*dims))[1] if q["kind"] == "fused"]
     assert p[0]["L"] == L
+
+
+@pytest.mark.parametrize("nz,dt,forward,backward", [(256, C64, "5", "2"), (512, C64, "18", "15"),
+                                                    (1024, C64, "7", "8"), (256, C128, "5", "4"),
+                                                    (60, C64, None, None)])
+def test_a_z_pass_that_others_follow_takes_the_y_choice(tmp_path, monkeypatch, nz, dt, forward, backward):
+    # a forward real plan ends with z, a backward one starts with it; lengths
+    # with no choice by axis take the same configuration in both
+    def z(d):
+        return [p for p in parse_describe(croft.croft_plan_describe_real(256, 256, nz, dt, d))[1] if p["axis"] == "z"][0]
+    f, b = z(-1)["candidate"], z(1)["candidate"]
+    assert (f, b) == (forward, backward) if forward else f == b
+    # a measured choice of the y axis stays with y
+    w = tmp_path / "w.txt"
+    w.write_text(f"{nz} 1 {dt} 1 0 1\n")
+    monkeypatch.setenv("CROFT_WISDOM", str(w))
+    assert z(1)["candidate"] == b
