@@ -482,9 +482,15 @@ __global__ void __launch_bounds__(Cfg::kBlock) fft_group_conv(const PassArgs a) 
             }
         }
     }
-    // the block's sum: a butterfly over each wavefront, then its wavefronts in order
+    // the block's sum: a butterfly over each wavefront, then its wavefronts in
+    // order.  A block need not be whole wavefronts (40 threads at 75 points
+    // complex128): what a shuffle returns from a lane past its end is undefined
+    // and stays out of the sum.
 #pragma unroll
-    for (int h = 32; h > 0; h /= 2) acc += __shfl_xor(acc, h, 64);
+    for (int h = 32; h > 0; h /= 2) {
+        const double peer = __shfl_xor(acc, h, 64);
+        if (butterfly_peer_exists(Cfg::kBlock, tid, h)) acc += peer;
+    }
     double *sum = reinterpret_cast<double *>(smem);
     __syncthreads();  // the exchange area is free
     if ((tid & 63) == 0) sum[tid >> 6] = acc;

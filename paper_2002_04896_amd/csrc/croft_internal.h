@@ -31,6 +31,10 @@ inline size_t element_bytes(int dtype) {
     return dtype == kC128 ? 16 : (dtype == kC64 ? 8 : 4);
 }
 
+// Whether the peer of thread `tid` in the step `h` (1 .. 32) of a butterfly over
+// its wavefront is a thread of the block (of `block` threads).
+constexpr bool butterfly_peer_exists(int block, int tid, int h) { return block % 64 == 0 || (tid ^ h) < block; }
+
 // How one axis pass is launched.  The kernels see a grid as lines of length n
 // (the transformed axis) with element stride `es` (in elements):
 //   contiguous (es == 1): line l starts at element l * n, l < nlines;
