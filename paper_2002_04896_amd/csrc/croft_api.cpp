@@ -218,8 +218,7 @@ bool lane_offset_fits(const PassLaunch &p, int dtype) {
 long long conv_partials_needed(const PassLaunch &pl, int dtype) {
     long long most = pass_tiles(pl);
     PassLaunch t = pl;
-    const int ncand = kernel_candidates(pl.n, kConvZ, dtype);
-    for (int c = 0; c < ncand; ++c)
+    for (int c : kernel_candidates(pl.n, kConvZ, dtype))
         if (select_kernel(pl.n, kConvZ, dtype, false, c, &t.cfg)) most = std::max(most, pass_tiles(t));
     if (select_generic_conv(pl.n, dtype, &t.cfg)) most = std::max(most, pass_tiles(t));
     return std::max(1LL, most);
@@ -713,7 +712,6 @@ int measure_passes(croft_plan *p) {
         for (PassLaunch &pl : ps) {
             const int wax = wisdom_axis(pl.kind, pl.axis);
             if (pl.cfg.generic || best.count({pl.n, pl.kind, wax})) continue;
-            const int ncand = kernel_candidates(pl.n, pl.kind, p->dtype);
             float best_ms = 1e30f;
             KernelConfig pick = pl.cfg;
             // every pass of the plan with this (length, kind, axis): a choice
@@ -723,7 +721,8 @@ int measure_passes(croft_plan *p) {
             for (auto &ps2 : p->passes)
                 for (const PassLaunch &q : ps2)
                     if (q.n == pl.n && q.kind == pl.kind && wisdom_axis(q.kind, q.axis) == wax) same.push_back(&q);
-            for (int c = 0; c < ncand && rc == CROFT_SUCCESS; ++c) {
+            for (int c : kernel_candidates(pl.n, pl.kind, p->dtype)) {
+                if (rc != CROFT_SUCCESS) break;
                 KernelConfig cfg;
                 if (!select_kernel(pl.n, pl.kind, p->dtype, false, c, &cfg) || cfg.candidate != c) continue;
                 bool fits = true;

@@ -115,8 +115,9 @@ struct Geometry {
 };
 
 // ---- kernels (croft_kernels.hip) ----
-// Number of compiled static configurations for (n, kind, dtype).
-int kernel_candidates(int n, int kind, int dtype);
+// The compiled static configurations for (n, kind, dtype): their candidate
+// numbers in increasing order, not always consecutive.
+std::vector<int> kernel_candidates(int n, int kind, int dtype);
 // The candidate of a strided pass that runs the grouped stages, -1 if none.
 int grouped_candidate(int n, int dtype);
 // Look up compiled configuration `cand` (0 = default; an unknown index falls

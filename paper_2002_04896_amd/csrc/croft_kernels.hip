@@ -332,10 +332,11 @@ int grouped_candidate(int n, int dtype) {
     return -1;
 }
 
-int kernel_candidates(int n, int kind, int dtype) {
-    int c = 0;
+std::vector<int> kernel_candidates(int n, int kind, int dtype) {
+    std::vector<int> c;
     for (const Entry &e : table())
-        if (e.n == n && e.kind == kind && e.dtype == dtype) ++c;
+        if (e.n == n && e.kind == kind && e.dtype == dtype) c.push_back(e.cand);
+    std::sort(c.begin(), c.end());
     return c;
 }
 
