@@ -157,13 +157,30 @@ void plain_in_cache(const PassLaunch &p, int dtype, int *cand, int *waves) {
     *waves = 0;
 }
 
+// Grid size of a pass that nothing was measured for (n, kind and dtype with no
+// built-in choice; 0: one block per tile, 1: one wave of resident blocks
+// looping over the tiles).  Up to 64 MiB a looping block's next loads are
+// served by the last-level cache under its stages; beyond, more blocks keep
+// memory busy (strided complex64 of 32 MiB, us, one block per tile against one
+// wave: 25 12.3, 11.4, 60 14.1, 12.9, 120 17.8, 15.9; of 0.8 GB moved 25 132,
+// 159, 150 149, 160; complex128 at 32 MiB 0.94 to 0.98 of the time, at 300 MiB
+// 1.02 to 1.09).  From 2048 points on a CU holds one block, whose loads only
+// the loop overlaps (300 MiB: complex64 x 4096 141, 94, y 897, 861 of 150
+// planes, FP16 x 2048 243, 210; complex128 x 2048 155, 115).  Contiguous lines
+// below 2048 are level at 32 MiB and faster with one block per tile beyond
+// (300 complex64 164, 141), but for complex128 at 720 (172, 148: one block on
+// a CU there too); 16-bit storage loops at 16 points and below (64 MiB, 0.96).
+int default_waves(const PassLaunch &p, int dtype) {
+    if (p.n >= 2048) return 1;
+    if (p.kind == kContiguous) return dtype == CROFT_C128 && p.n == 720 ? 1 : 0;
+    const long long bytes = p.nlines * p.nw * p.n * (long long)element_bytes(dtype);
+    return bytes <= (64LL << 20) && (!is_half(dtype) || p.n <= 16) ? 1 : 0;
+}
+
 // The configuration a contiguous or strided pass starts from: a measured
 // choice; for FP32 and FP64 rows that are not whole lines the grouped stages,
 // whose tile order keeps the shared lines in one L2 (croft_group.h has the
-// figures); a built-in choice; else candidate 0, one block per tile (0.8 GB
-// moved, complex64, against one wave of resident blocks looping over the
-// tiles: strided 25 132 us against 159, 150 149 against 160, 300 contiguous
-// 141 against 164; below 24 MB level).
+// figures); a built-in choice; else candidate 0 on default_waves.
 // z_first: a z pass that other passes follow (a backward real plan's) takes
 // the built-in choice of the y axis: z's own is for the pass that nothing
 // follows, and its non-temporal stores send the spectrum past the last-level
@@ -174,12 +191,14 @@ void plain_in_cache(const PassLaunch &p, int dtype, int *cand, int *waves) {
 // 107.6, 93.5).
 void pass_choice(const PassLaunch &p, int dtype, int dir, int *cand, int *waves, bool z_first = false) {
     const int axis = wisdom_axis(p.kind, p.axis);
-    *cand = *waves = 0;
+    *cand = 0;
+    *waves = default_waves(p, dtype);
     if (wisdom_measured(p.n, p.kind, dtype, axis, cand, waves)) return;
     if (p.kind == kStrided && !is_half(dtype) && partial_lines(p, dtype)) {
         const int g = grouped_candidate(p.n, dtype);
         if (g >= 0) {
             *cand = g;
+            *waves = 0;
             return;
         }
     }
@@ -314,7 +333,7 @@ int build_unfused_passes(const Geometry &g, int dtype, int dir, int flags, std::
         p.es = 1;
         p.nlines = N / p.n;
         p.nw = 1;
-        int cand = 0, waves = 0;
+        int cand = 0, waves = default_waves(p, dtype);
         wisdom_lookup(p.n, kContiguous, dtype, dir, -1, &cand, &waves);
         const bool generic = (flags & CROFT_FORCE_GENERIC) != 0 || p.n == 1;
         if (!select_kernel(p.n, kContiguous, dtype, generic, cand, &p.cfg)) return no_kernel(p.n, dtype);
@@ -344,9 +363,15 @@ int build_real_passes(const Geometry &g, int dtype, int dir, int flags, std::vec
     xp.kind = kRealX;
     xp.es = 1;
     xp.nlines = (long long)g.ny * g.nz;
-    // one block per tile where nothing was measured (complex128 160 x 144 x 150
-    // backward 49.0 -> 43.3 us against one wave of resident blocks)
-    int cand = 0, waves = 0;
+    // where nothing was measured: one block per tile below 480 points
+    // (complex128 160 x 144 x 150 backward 43.3 us against 49.0 on one wave of
+    // resident blocks; 96 points of 96 MiB 131 against 139), one wave from there on,
+    // where a CU holds few blocks (complex64 768 229, 217 backward, complex128
+    // 960 330, 296 forward, 2048 345, 288), but for complex64 720 forward (251,
+    // 278) and complex128 576 backward (325, 343)
+    const bool one_wave = m >= 480 && !(dtype == CROFT_C64 && m == 720 && tune_dir != CROFT_BACKWARD) &&
+                          !(dtype == CROFT_C128 && m == 576 && tune_dir == CROFT_BACKWARD);
+    int cand = 0, waves = one_wave ? 1 : 0;
     wisdom_lookup(m, kRealX, dtype, tune_dir, -1, &cand, &waves);
     if (!select_kernel(m, kRealX, dtype, false, cand, &xp.cfg))
         return fail(CROFT_ERR_UNSUPPORTED_SIZE, "no real x kernel for nx = %d (half length %d)", g.nx, m);
