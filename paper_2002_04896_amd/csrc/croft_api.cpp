@@ -141,20 +141,34 @@ int no_kernel(int n, int dtype) {
 // True where the rows of a strided pass are not whole 128-byte lines.
 bool partial_lines(const PassLaunch &p, int dtype) { return (p.es * (long long)element_bytes(dtype)) % 128 != 0; }
 
+// Bytes of the elements a pass reads.
+long long pass_bytes(const PassLaunch &p, int dtype) {
+    return p.nlines * p.nw * p.n * (long long)element_bytes(dtype);
+}
+
 // A built-in non-temporal first pass gives way to the plain tile (padded where
 // there is one, candidate 1) where the grid stays in the 256 MB last-level
 // cache, from which the next pass reads it (us, both directions, non-temporal
 // against plain: complex64 384 x 96 x 100 41.8, 33.1, 512 x 96 x 100 49.9,
-// 42.2, 640 x 200 x 160 206, 181, 512 x 320 x 300 (393 MB) 451, 465; complex128
-// 128^3 39.4, 33.3, 512 x 96 x 100 87, 82, 512 x 200 x 160 (262 MB) 263, 269,
-// 512 x 320 x 300 942, 981).
+// 42.2, 640 x 200 x 160 186, 168, 512 x 256 x 256 (256 MiB) 253, 248, 512 x 320
+// x 300 (393 MB) 451, 465; complex128 128^3 39.4, 33.3, 512 x 96 x 100 87, 78,
+// 512 x 160 x 128 (160 MiB) 168, 165, 512 x 320 x 300 942, 981).  Near that
+// size complex128 grids whose other axes are not powers of two lose their
+// lines earlier: 512 x 200 x 128 (200 MiB) 204.5, 205.1, 512 x 192 x 160 246,
+// 254, 512 x 200 x 160 (250 MiB) 253, 264, 640 x 160 x 144 248, 256, against
+// 512 x 128 x 256 (256 MiB) 252, 250, 256^3 259, 254, 256 x 256 x 192 200, 190.
+// Up to 64 MiB the plain tile loops (32 MiB: complex64 1024 17.4, 15.9, 512
+// 15.1, 13.8, 384 16.4, 15.9).
 constexpr long long kCacheBytes = 256LL << 20;
 constexpr int kStreamingLines = 3;  // its candidate number
 void plain_in_cache(const PassLaunch &p, int dtype, int *cand, int *waves) {
     if (p.kind != kContiguous || is_half(dtype) || *cand != kStreamingLines) return;
-    if (p.nlines * (long long)p.n * (long long)element_bytes(dtype) > kCacheBytes) return;
+    const bool pow2 = (p.nlines & (p.nlines - 1)) == 0;
+    const long long limit = dtype == CROFT_C128 && !pow2 && p.n > 256 ? 192LL << 20 : kCacheBytes;
+    const long long bytes = pass_bytes(p, dtype);
+    if (bytes > limit) return;
     *cand = 1;
-    *waves = 0;
+    *waves = bytes <= (64LL << 20) ? 1 : 0;
 }
 
 // Grid size of a pass that nothing was measured for (n, kind and dtype with no
@@ -173,14 +187,14 @@ void plain_in_cache(const PassLaunch &p, int dtype, int *cand, int *waves) {
 int default_waves(const PassLaunch &p, int dtype) {
     if (p.n >= 2048) return 1;
     if (p.kind == kContiguous) return dtype == CROFT_C128 && p.n == 720 ? 1 : 0;
-    const long long bytes = p.nlines * p.nw * p.n * (long long)element_bytes(dtype);
-    return bytes <= (64LL << 20) && (!is_half(dtype) || p.n <= 16) ? 1 : 0;
+    return pass_bytes(p, dtype) <= (64LL << 20) && (!is_half(dtype) || p.n <= 16) ? 1 : 0;
 }
 
 // The configuration a contiguous or strided pass starts from: a measured
-// choice; for FP32 and FP64 rows that are not whole lines the grouped stages,
-// whose tile order keeps the shared lines in one L2 (croft_group.h has the
-// figures); a built-in choice; else candidate 0 on default_waves.
+// choice; a built-in choice for its size; for FP32 and FP64 rows that are not
+// whole lines the grouped stages, whose tile order keeps the shared lines in
+// one L2 (croft_group.h has the figures); a built-in choice; else candidate 0
+// on default_waves.
 // z_first: a z pass that other passes follow (a backward real plan's) takes
 // the built-in choice of the y axis: z's own is for the pass that nothing
 // follows, and its non-temporal stores send the spectrum past the last-level
@@ -194,6 +208,11 @@ void pass_choice(const PassLaunch &p, int dtype, int dir, int *cand, int *waves,
     *cand = 0;
     *waves = default_waves(p, dtype);
     if (wisdom_measured(p.n, p.kind, dtype, axis, cand, waves)) return;
+    const int builtin_axis = z_first && axis == 2 ? 1 : axis;
+    const long long row_lines = (p.es * (long long)element_bytes(dtype) + 127) / 128;
+    const PassSize size{pass_bytes(p, dtype), p.kind == kStrided ? row_lines * p.nw : 0,
+                        p.kind == kStrided && partial_lines(p, dtype)};
+    if (sized_choice(p.n, p.kind, dtype, builtin_axis, size, cand, waves)) return;
     if (p.kind == kStrided && !is_half(dtype) && partial_lines(p, dtype)) {
         const int g = grouped_candidate(p.n, dtype);
         if (g >= 0) {
@@ -202,7 +221,7 @@ void pass_choice(const PassLaunch &p, int dtype, int dir, int *cand, int *waves,
             return;
         }
     }
-    builtin_choice(p.n, p.kind, dtype, dir, z_first && axis == 2 ? 1 : axis, cand, waves);
+    builtin_choice(p.n, p.kind, dtype, dir, builtin_axis, cand, waves);
     plain_in_cache(p, dtype, cand, waves);
 }
 

@@ -196,6 +196,15 @@ hipError_t noalloc_scratch(int device, int8_t **ptr);
 bool wisdom_lookup(int n, int kind, int dtype, int dir, int axis, int *cand, int *waves);
 // Its built-in part alone.
 bool builtin_choice(int n, int kind, int dtype, int dir, int axis, int *cand, int *waves);
+// What a built-in choice for a size goes by: the bytes a pass reads and, strided,
+// its 128-byte row segments (a tile is one to two of them wide) and whether
+// rows end inside a 128-byte line.
+struct PassSize {
+    long long bytes = 0, segments = 0;
+    bool partial_lines = false;
+};
+// The built-in choices that hold for some sizes only; before builtin_choice.
+bool sized_choice(int n, int kind, int dtype, int axis, const PassSize &size, int *cand, int *waves);
 // The part of it that was measured for this process or its CROFT_WISDOM file
 // (no built-in choice).
 bool wisdom_measured(int n, int kind, int dtype, int axis, int *cand, int *waves);

@@ -12,7 +12,8 @@
 // serves every axis.  Lookup order: the CROFT_WISDOM file, choices measured
 // in this process, for forward plans the forward-only built-in choices, the
 // per-axis built-in choices, the built-in table below (measured on an MI355X
-// with CROFT_MEASURE on cubic grids; kinds 2 and 3, the real x pass and the
+// with CROFT_MEASURE on cubic grids, and before it the choices that hold for
+// some sizes only; kinds 2 and 3, the real x pass and the
 // fused multiply pass, on real and convolution plans of cubic grids), then
 // candidate 0 on the grid size the caller starts from.  At each step an entry for the pass's
 // axis comes before one for any axis.
@@ -155,6 +156,34 @@ const BuiltinAxis kBuiltinAxis[] = {
     {512, 1, 3, 2, 20, 1},
 };
 
+// Choices for some sizes only, looked up before the tables above: the first
+// entry whose limits hold.  axis -1: any; rows 0: any, 1: whole 128-byte
+// lines, 2: not; segments: at most so many 128-byte row segments (0: no
+// limit); MiB the pass reads: more than `above`, at most `upto` (0: no limit).
+struct BuiltinSized {
+    int n, kind, dtype, axis, rows, segments, above, upto, cand, waves;
+};
+constexpr int kAny = 0, kWhole = 1;
+const BuiltinSized kBuiltinSized[] = {
+    // 256: the wide tiles of the choices by axis leave most CUs without one on
+    // small grids (us, wide against 16 or 8 lines: complex64 y 64 x 256 x 16
+    // 8.1, 6.4, 64 x 256 x 64 (256 segments, the whole transform) 20.1, 19.8, z
+    // 64 x 16 x 256 8.4, 6.8; complex128 y 64 x 256 x 8 7.8, 6.4, 64 x 256 x 32
+    // 9.3, 8.2, 64 x 256 x 64 (512, whole) 35.1, 33.1)
+    {256, 1, 0, 1, kWhole, 128, 0, 0, 1, 0},
+    {256, 1, 0, 2, kWhole, 128, 0, 0, 1, 0},
+    {256, 1, 1, 1, kWhole, 512, 0, 0, 0, 1},
+    // complex64 384 beyond the cache: the 32-line wide tile on one wave (whole
+    // transforms, us, against the grouped stages: 384^3 496, 516, 384 x 384 x 256
+    // 357, 363; in the cache 384 x 384 x 96 124, 123, 64 x 384 x 160 47, 44)
+    {384, 1, 0, -1, kWhole, 0, 256, 0, 2, 1},
+    // complex128 y at 512 around the cache's size: two waves (whole transforms,
+    // us, one block per tile against it: 512 x 512 x 48 (192 MiB) 208, 202, 512 x
+    // 512 x 64 287, 276, 512 x 512 x 96 414, 405; 128 MiB 146.3, 146.3, 512 MiB
+    // 571, 570)
+    {512, 1, 1, 1, kWhole, 0, 160, 400, 4, 2},
+};
+
 std::mutex g_mu;
 std::map<std::tuple<int, int, int, int>, std::pair<int, int>> g_mem;  // (n, kind, dtype, axis or -1)
 
@@ -201,6 +230,19 @@ bool wisdom_measured(int n, int kind, int dtype, int axis, int *cand, int *waves
 bool wisdom_lookup(int n, int kind, int dtype, int dir, int axis, int *cand, int *waves) {
     return wisdom_measured(n, kind, dtype, axis, cand, waves) ||
            builtin_choice(n, kind, dtype, dir, axis, cand, waves);
+}
+
+bool sized_choice(int n, int kind, int dtype, int axis, const PassSize &size, int *cand, int *waves) {
+    for (const BuiltinSized &b : kBuiltinSized) {
+        if (b.n != n || b.kind != kind || b.dtype != dtype || (b.axis >= 0 && b.axis != axis)) continue;
+        if (b.rows != kAny && (b.rows == kWhole) == size.partial_lines) continue;
+        if (b.segments && size.segments > b.segments) continue;
+        if (size.bytes <= ((long long)b.above << 20) || (b.upto && size.bytes > ((long long)b.upto << 20))) continue;
+        *cand = b.cand;
+        *waves = b.waves;
+        return true;
+    }
+    return false;
 }
 
 bool builtin_choice(int n, int kind, int dtype, int dir, int axis, int *cand, int *waves) {

@@ -33,3 +33,23 @@ def test_real_x_grid_size(m, dt, forward, backward):
     got = [[p for p in parse_describe(croft.croft_plan_describe_real(2 * m, 8, 8, dt, d))[1] if p["kind"] == "real"][0]
            for d in (-1, 1)]
     assert (got[0]["waves"], got[1]["waves"]) == (forward, backward)
+
+
+@pytest.mark.parametrize("dims,cand", [((512, 200, 160), "3"), ((512, 128, 100), "1"), ((512, 160, 128), "1"),
+                                       ((512, 256, 128), "1"), ((640, 160, 144), "3"), ((512, 200, 120), "1")])
+def test_complex128_streaming_first_pass(dims, cand):
+    # beyond 192 MiB on uneven grids, beyond 256 MiB on powers of two
+    assert one("x", *dims, C128)["candidate"] == cand
+
+
+@pytest.mark.parametrize("axis,dims,dt,choice", [
+    ("y", (64, 256, 32), C64, ("1", "0")), ("y", (64, 256, 33), C64, ("2", "0")),
+    ("z", (64, 32, 256), C64, ("1", "0")), ("z", (64, 33, 256), C64, ("5", "0")),
+    ("y", (64, 256, 64), C128, ("0", "1")), ("y", (64, 256, 65), C128, ("4", "0")),
+    ("y", (384, 384, 384), C64, ("2", "1")), ("z", (384, 384, 384), C64, ("2", "1")),
+    ("y", (384, 384, 96), C64, ("8", "0")), ("y", (383, 384, 384), C64, ("8", "0")),
+    ("y", (512, 512, 64), C128, ("4", "2")), ("y", (512, 512, 512), C128, ("4", "0")),
+    ("y", (512, 512, 32), C128, ("4", "0"))])
+def test_choices_by_size(axis, dims, dt, choice):
+    p = one(axis, *dims, dt)
+    assert (p["candidate"], p["waves"]) == choice
