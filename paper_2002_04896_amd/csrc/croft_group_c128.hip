@@ -14,10 +14,16 @@ namespace dev {
 #define SHORT(N) make_entry<N, kStrided, StC128, 16, kC128>(0),
 #define LINES(N) make_entry<N, kContiguous, StC128, 16, kC128>(0),
 
+// strided 1: the stage-by-stage tile, in the XCD-contiguous order but at 384, taken where the launch has few
+// tiles and at some sizes of 384, 400 and 480 (kBuiltinSized in croft_tune.cpp)
+#define STAGED(N) make_entry<N, kStrided, StC128, 16, kC128, 0, 0, 0, 1, 0, 1>(1),
+
 std::vector<Entry> group_entries_c128() {
     return {
         CROFT_GROUP_LONG(STRIDED)
         make_group_entry<384, StC128, 16, kC128, kStrided>(0),
+        STAGED(320) STAGED(360) STAGED(400) STAGED(480) STAGED(576) STAGED(640) STAGED(768) STAGED(960)
+        make_entry<384, kStrided, StC128, 16, kC128>(1),
         CROFT_GROUP_SHORT(SHORT)
         CROFT_GROUP_PARTIAL(PARTIAL)
         // the same at 128 and 256: 6, beside the candidates of croft_entries_c128.hip

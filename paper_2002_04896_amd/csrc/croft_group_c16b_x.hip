@@ -9,8 +9,13 @@ namespace dev {
 // (283), 960 198 (240).  1000 (three trips) stays stage by stage: 251 against 290
 #define LINES(N) make_group_entry<N, StHalf<true>, 4, kC16B, kContiguous>(0),
 
+// contiguous 1: the stage-by-stage tile, taken on small grids (kBuiltinSized in croft_tune.cpp)
+#define STAGED(N) make_entry<N, kContiguous, StHalf<true>, 4, kC16B>(1),
+
 std::vector<Entry> group_entries_c16b_x() {
     return {
+        STAGED(96) STAGED(100) STAGED(160) STAGED(192) STAGED(200) STAGED(288) STAGED(320) STAGED(360) STAGED(384)
+        STAGED(480) STAGED(640) STAGED(768) STAGED(960)
         LINES(72) LINES(80) LINES(96) LINES(100) LINES(120) LINES(160) LINES(192) LINES(200) LINES(240) LINES(384)
         LINES(75) LINES(81) LINES(90) LINES(108) LINES(125) LINES(135) LINES(144) LINES(150) LINES(162) LINES(180)
         LINES(216) LINES(225)

@@ -160,10 +160,12 @@ const BuiltinAxis kBuiltinAxis[] = {
 // entry whose limits hold.  axis -1: any; rows 0: any, 1: whole 128-byte
 // lines, 2: not; segments: at most so many 128-byte row segments (0: no
 // limit); MiB the pass reads: more than `above`, at most `upto` (0: no limit).
+// dtype kHalves: either 16-bit storage.
 struct BuiltinSized {
     int n, kind, dtype, axis, rows, segments, above, upto, cand, waves;
 };
-constexpr int kAny = 0, kWhole = 1;
+constexpr int kAny = 0, kWhole = 1, kPartial = 2;
+constexpr int kHalves = -1;
 const BuiltinSized kBuiltinSized[] = {
     // 256: the wide tiles of the choices by axis leave most CUs without one on
     // small grids (us, wide against 16 or 8 lines: complex64 y 64 x 256 x 16
@@ -182,6 +184,68 @@ const BuiltinSized kBuiltinSized[] = {
     // 512 x 64 287, 276, 512 x 512 x 96 414, 405; 128 MiB 146.3, 146.3, 512 MiB
     // 571, 570)
     {512, 1, 1, 1, kWhole, 0, 160, 400, 4, 2},
+    // Strided launches of few tiles: the stage-by-stage tiles, whose lines have
+    // more threads, against the grouped stages, whose threads hold up to 64
+    // elements and take longest over a tile (a pass, us, stage by stage against
+    // grouped, at about a quarter of the limit | at the limit | beyond it:
+    // complex64 320 7.0, 8.6 | 8.2, 9.8 | 14.6, 13.2; 960 8.7, 13.7 | 10.2, 14.9 |
+    // 17.0, 15.6; complex128 320 0.88 | 0.91 | 1.12 of the time, 768 0.77 | 0.91 |
+    // 1.04; FP16 100 6.4, 7.0 | 0.95 | 1.07, 256 8.5, 9.4 | 11.5,
+    // 13.3 | 26.2, 18.7, 320 0.67 | 0.84 |
+    // 1.00, 900 0.60 | 0.78 | 1.01)
+    {288, 1, 0, -1, kAny, 256, 0, 0, 1, 0}, {320, 1, 0, -1, kAny, 256, 0, 0, 1, 0},
+    {360, 1, 0, -1, kAny, 256, 0, 0, 1, 0}, {400, 1, 0, -1, kAny, 256, 0, 0, 1, 0},
+    {480, 1, 0, -1, kAny, 256, 0, 0, 1, 0}, {576, 1, 0, -1, kAny, 128, 0, 0, 1, 0},
+    {640, 1, 0, -1, kAny, 128, 0, 0, 1, 0}, {720, 1, 0, -1, kAny, 128, 0, 0, 1, 0},
+    {768, 1, 0, -1, kAny, 128, 0, 0, 1, 0}, {960, 1, 0, -1, kAny, 128, 0, 0, 1, 0},
+    {320, 1, 1, -1, kAny, 256, 0, 0, 1, 0}, {360, 1, 1, -1, kAny, 256, 0, 0, 1, 0},
+    {384, 1, 1, -1, kPartial, 256, 0, 0, 1, 0}, {400, 1, 1, -1, kAny, 256, 0, 0, 1, 0},
+    {480, 1, 1, -1, kAny, 256, 0, 0, 1, 0}, {576, 1, 1, -1, kAny, 128, 0, 0, 1, 0},
+    {640, 1, 1, -1, kAny, 128, 0, 0, 1, 0}, {768, 1, 1, -1, kAny, 512, 0, 0, 1, 0},
+    {960, 1, 1, -1, kAny, 128, 0, 0, 1, 0},
+    {32, 1, kHalves, -1, kWhole, 8192, 0, 0, 1, 0}, {60, 1, kHalves, -1, kWhole, 1024, 0, 0, 1, 0},
+    {60, 1, kHalves, -1, kPartial, 256, 0, 0, 1, 0}, {64, 1, kHalves, -1, kWhole, 4096, 0, 0, 1, 0},
+    {64, 1, kHalves, -1, kPartial, 256, 0, 0, 1, 0}, {80, 1, kHalves, -1, kWhole, 512, 0, 0, 1, 0},
+    {80, 1, kHalves, -1, kPartial, 128, 0, 0, 1, 0}, {96, 1, kHalves, -1, kWhole, 512, 0, 0, 1, 0},
+    {96, 1, kHalves, -1, kPartial, 128, 0, 0, 1, 0}, {100, 1, kHalves, -1, kWhole, 256, 0, 0, 1, 0},
+    {100, 1, kHalves, -1, kPartial, 128, 0, 0, 1, 0}, {120, 1, kHalves, -1, kWhole, 512, 0, 0, 1, 0},
+    {120, 1, kHalves, -1, kPartial, 128, 0, 0, 1, 0},
+    {256, 1, kHalves, -1, kWhole, 512, 0, 0, 0, 0}, {160, 1, kHalves, -1, kPartial, 128, 0, 0, 1, 0}, {192, 1, kHalves, -1, kWhole, 512, 0, 0, 1, 0},
+    {192, 1, kHalves, -1, kPartial, 128, 0, 0, 1, 0}, {200, 1, kHalves, -1, kAny, 128, 0, 0, 1, 0},
+    {288, 1, kHalves, -1, kAny, 128, 0, 0, 1, 0}, {320, 1, kHalves, -1, kAny, 256, 0, 0, 1, 0},
+    {360, 1, kHalves, -1, kAny, 128, 0, 0, 1, 0}, {384, 1, kHalves, -1, kAny, 128, 0, 0, 1, 0},
+    {400, 1, kHalves, -1, kAny, 128, 0, 0, 1, 0}, {480, 1, kHalves, -1, kAny, 128, 0, 0, 1, 0},
+    {576, 1, kHalves, -1, kAny, 64, 0, 0, 1, 0}, {640, 1, kHalves, -1, kAny, 64, 0, 0, 1, 0},
+    {720, 1, kHalves, -1, kAny, 32, 0, 0, 1, 0}, {768, 1, kHalves, -1, kAny, 64, 0, 0, 1, 0},
+    {900, 1, kHalves, -1, kAny, 64, 0, 0, 1, 0}, {960, 1, kHalves, -1, kAny, 64, 0, 0, 1, 0},
+    {972, 1, kHalves, -1, kAny, 32, 0, 0, 1, 0},
+    // 16-bit 128 in whole rows, whole transforms: along z at every size (512 x 512 x
+    // 128 179, 187, 256 x 512 x 128 92, 97, 250 x 1024 x 128 192, 190), along y up to
+    // 64 MiB (128 x 128 x 128 21.1, 23.2, 128 x 128 x 1024 88, 91)
+    {128, 1, kHalves, 2, kWhole, 0, 0, 0, 1, 4}, {128, 1, kHalves, 1, kWhole, 0, 0, 64, 1, 1},
+    // and at every size of whole rows at 16-bit 160 (one wave: 64 x 160 x 768 19.5,
+    // 22.6; 250 x 768 x 160 57.4, 59.0) and complex128 384 (one wave: 384 x 384 x
+    // 48 38.9, 45.5, 64 x 768 x 384 120, 128); at complex128 480 up to 64 MiB (64 x
+    // 480 x 64 15.7, 17.2; 120 MiB 42.5, 41.9) and along y beyond the cache, as at
+    // 400, in the XCD-contiguous order (64 x 480 x 640 110, 127, 384 x 480 x 96 107,
+    // 117, 64 x 400 x 768 119, 129)
+    {160, 1, kHalves, -1, kWhole, 0, 0, 0, 1, 1},
+    {384, 1, 1, -1, kWhole, 0, 0, 0, 1, 1},
+    {480, 1, 1, -1, kWhole, 0, 0, 64, 1, 0},
+    {480, 1, 1, 1, kWhole, 0, 256, 0, 1, 0},
+    {400, 1, 1, 1, kWhole, 0, 256, 0, 1, 0},
+    // 16-bit contiguous lines of small grids, likewise (7 MiB: 100 11.4, 12.4,
+    // 160 11.0, 12.7, 288 10.1, 13.1, 480 10.3, 12.4, 960 (2 MiB) 7.8, 8.7; 28 MiB:
+    // 96 16.1, 18.4, 192 18.3, 21.4, 360 22.2, 23.6, 480 23.0, 24.7; 72 to 120 MiB:
+    // 288 48.9, 47.4, 360 54.9, 48.6, 480 69.4, 61.3), at 640 at every size
+    // (160 MiB 84, 90)
+    {96, 0, kHalves, -1, kAny, 0, 0, 64, 1, 0}, {100, 0, kHalves, -1, kAny, 0, 0, 64, 1, 0},
+    {160, 0, kHalves, -1, kAny, 0, 0, 64, 1, 0}, {192, 0, kHalves, -1, kAny, 0, 0, 64, 1, 0},
+    {200, 0, kHalves, -1, kAny, 0, 0, 64, 1, 0}, {288, 0, kHalves, -1, kAny, 0, 0, 64, 1, 0},
+    {320, 0, kHalves, -1, kAny, 0, 0, 64, 1, 0}, {360, 0, kHalves, -1, kAny, 0, 0, 32, 1, 0},
+    {384, 0, kHalves, -1, kAny, 0, 0, 64, 1, 0}, {480, 0, kHalves, -1, kAny, 0, 0, 32, 1, 0},
+    {640, 0, kHalves, -1, kAny, 0, 0, 0, 1, 1}, {768, 0, kHalves, -1, kAny, 0, 0, 16, 1, 0},
+    {960, 0, kHalves, -1, kAny, 0, 0, 4, 1, 0},
 };
 
 std::mutex g_mu;
@@ -234,7 +298,7 @@ bool wisdom_lookup(int n, int kind, int dtype, int dir, int axis, int *cand, int
 
 bool sized_choice(int n, int kind, int dtype, int axis, const PassSize &size, int *cand, int *waves) {
     for (const BuiltinSized &b : kBuiltinSized) {
-        if (b.n != n || b.kind != kind || b.dtype != dtype || (b.axis >= 0 && b.axis != axis)) continue;
+        if (b.n != n || b.kind != kind || (b.dtype == kHalves ? dtype < kC16F : b.dtype != dtype) || (b.axis >= 0 && b.axis != axis)) continue;
         if (b.rows != kAny && (b.rows == kWhole) == size.partial_lines) continue;
         if (b.segments && size.segments > b.segments) continue;
         if (size.bytes <= ((long long)b.above << 20) || (b.upto && size.bytes > ((long long)b.upto << 20))) continue;

@@ -53,3 +53,27 @@ def test_complex128_streaming_first_pass(dims, cand):
 def test_choices_by_size(axis, dims, dt, choice):
     p = one(axis, *dims, dt)
     assert (p["candidate"], p["waves"]) == choice
+
+
+# the last launch that takes the stage-by-stage tile and the first that takes
+# the grouped stages (candidate 0), in whole rows and in partial ones
+@pytest.mark.parametrize("n,dt,few,many", [
+    (288, C64, (64, 64), (64, 65)), (960, C64, (64, 32), (64, 33)), (960, C64, (45, 42), (45, 43)),
+    (320, C128, (64, 32), (64, 33)), (768, C128, (64, 64), (64, 65)), (384, C128, (45, 42), (45, 43)),
+    (64, F16, (64, 2048), (64, 2049)), (64, BF16, (45, 128), (45, 129)), (100, F16, (64, 128), (64, 129)),
+    (320, BF16, (64, 128), (64, 129)), (972, F16, (64, 16), (64, 17))])
+def test_launches_of_few_tiles_run_stage_by_stage(n, dt, few, many):
+    assert one("y", few[0], n, few[1], dt)["candidate"] == "1"
+    assert one("y", many[0], n, many[1], dt)["candidate"] == "0"
+
+
+@pytest.mark.parametrize("axis,dims,dt,choice", [
+    ("y", (64, 160, 4096), F16, ("1", "1")), ("z", (512, 512, 128), BF16, ("1", "4")), ("y", (64, 128, 2048), F16, ("1", "1")),
+    ("y", (64, 128, 2049), F16, ("6", "0")), ("y", (45, 128, 8), F16, ("6", "0")), ("y", (64, 256, 256), BF16, ("0", "0")),
+    ("y", (64, 256, 257), BF16, ("6", "0")), ("y", (45, 160, 200), BF16, ("0", None)), ("z", (64, 800, 384), C128, ("1", "1")),
+    ("y", (64, 480, 136), C128, ("1", "0")), ("y", (64, 480, 140), C128, ("0", None)), ("y", (64, 480, 640), C128, ("1", "0")),
+    ("z", (64, 640, 480), C128, ("0", None)), ("x", (288, 32, 1820), F16, ("1", "0")),
+    ("x", (288, 32, 1821), F16, ("0", "0")), ("x", (640, 64, 4096), BF16, ("1", "1")), ("x", (640, 320, 400), C64, ("3", "0"))])
+def test_where_the_stage_by_stage_tiles_stay(axis, dims, dt, choice):
+    p = one(axis, *dims, dt)
+    assert p["candidate"] == choice[0] and choice[1] in (None, p["waves"])
