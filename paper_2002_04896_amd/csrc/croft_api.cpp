@@ -292,6 +292,7 @@ int build_passes(const Geometry &g, int dtype, int dir, int flags, std::vector<P
         if (!lane_offset_fits(p, dtype) && !select_kernel(n, p.kind, dtype, true, 0, &p.cfg))
             return no_kernel(n, dtype);
         plain_on_partial_lines(p, dtype, &p.cfg);
+        spread_few_lines(&p, dtype);
         p.cfg.grid_waves = waves;
         if (half) {
             ExpMap &m = p.em;
@@ -358,6 +359,7 @@ int build_unfused_passes(const Geometry &g, int dtype, int dir, int flags, std::
         if (!select_kernel(p.n, kContiguous, dtype, generic, cand, &p.cfg)) return no_kernel(p.n, dtype);
         if (!lane_offset_fits(p, dtype) && !select_kernel(p.n, kContiguous, dtype, true, 0, &p.cfg))
             return no_kernel(p.n, dtype);
+        spread_few_lines(&p, dtype);
         p.cfg.grid_waves = waves;
         out->push_back(p);
     }
@@ -412,6 +414,7 @@ int build_real_passes(const Geometry &g, int dtype, int dir, int flags, std::vec
         if (!lane_offset_fits(p, dtype) && !select_kernel(n, kStrided, dtype, true, 0, &p.cfg))
             return no_kernel(n, dtype);
         plain_on_partial_lines(p, dtype, &p.cfg);
+        spread_few_lines(&p, dtype);
         p.cfg.grid_waves = waves;
         yz.push_back(p);
     }

@@ -126,6 +126,9 @@ int grouped_candidate(int n, int dtype);
 bool select_kernel(int n, int kind, int dtype, bool force_generic, int cand, KernelConfig *cfg);
 // Tiles (blocks of work) of one launch of a pass.
 long long pass_tiles(const PassLaunch &pl);
+// Bluestein passes of at most one tile a CU take the kernel with more threads
+// per line (croft_bluestein.hip has the figures); other passes are left alone.
+void spread_few_lines(PassLaunch *pl, int dtype);
 // Launch one pass.  `in`/`out` point at the first element of the lines the
 // launch covers; exponent pointers likewise (half storage only).
 // mul / partial: the multiplier and the energy partials of a kConvZ pass.
@@ -240,12 +243,13 @@ int bluestein_length(int n);
 // The Bluestein kernel of a pass kind and dtype whose convolution has length
 // m (a power of two, 16 .. 8192) with its launch shape: T threads per line,
 // L lines per block, LDS bytes; func is NULL for any other m and where two
-// line buffers do not fit in LDS (FP64 at 8192).
+// line buffers do not fit in LDS (FP64 at 8192).  few_tiles: the shape for
+// launches of at most one tile a CU.
 struct BluesteinLaunch {
     const void *func = nullptr;
     int T = 0, L = 0;
     size_t lds = 0;
 };
-BluesteinLaunch bluestein_kernel(int kind, int dtype, int m);
+BluesteinLaunch bluestein_kernel(int kind, int dtype, int m, bool few_tiles);
 
 }  // namespace croft

@@ -374,7 +374,7 @@ bool select_kernel(int n, int kind, int dtype, bool force_generic, int cand, Ker
         // Bluestein: the kernel compiled for the convolution length m
         const int m = bluestein_length(n);
         const RPlan pm = make_rplan(m);
-        const BluesteinLaunch bl = bluestein_kernel(kind, dtype, m);
+        const BluesteinLaunch bl = bluestein_kernel(kind, dtype, m, false);
         if (!bl.func || pm.S < 0) return false;
         const int T = bl.T, L = bl.L;
         cfg->func = cfg->func_inv = bl.func;
@@ -439,6 +439,17 @@ long long pass_tiles(const PassLaunch &pl) {
     const int L = pl.cfg.lines;
     if (!strided_kind(pl.kind)) return (pl.nlines + L - 1) / L;
     return ((pl.es + L - 1) / L) * pl.nw;
+}
+
+void spread_few_lines(PassLaunch *pl, int dtype) {
+    constexpr long long kCUs = 256;
+    if (!pl->cfg.bluestein || pass_tiles(*pl) > kCUs) return;
+    const BluesteinLaunch bl = bluestein_kernel(pl->kind, dtype, pl->cfg.bluestein, true);
+    pl->cfg.func = pl->cfg.func_inv = bl.func;
+    pl->cfg.threads_per_line = bl.T;
+    pl->cfg.lines = bl.L;
+    pl->cfg.block = ((bl.T * bl.L + 63) / 64) * 64;
+    pl->cfg.lds = bl.lds;
 }
 
 long long pass_blocks(const PassLaunch &pl) {

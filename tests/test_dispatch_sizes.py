@@ -77,3 +77,12 @@ def test_launches_of_few_tiles_run_stage_by_stage(n, dt, few, many):
 def test_where_the_stage_by_stage_tiles_stay(axis, dims, dt, choice):
     p = one(axis, *dims, dt)
     assert p["candidate"] == choice[0] and choice[1] in (None, p["waves"])
+
+
+@pytest.mark.parametrize("axis,few,many,dt,T", [
+    ("y", (64, 1021, 8), (64, 1021, 9), C64, ("256", "128")), ("x", (1021, 32, 16), (1021, 19, 27), F16, ("256", "128")),
+    ("y", (64, 2039, 8), (64, 2039, 9), BF16, ("256", "128")), ("z", (64, 32, 211), (64, 33, 211), C64, ("64", "32")),
+    ("y", (64, 97, 64), (64, 97, 65), C128, ("32", "16")), ("y", (64, 509, 2), (64, 509, 640), C64, ("64", "64"))])
+def test_bluestein_spreads_few_lines_over_more_threads(axis, few, many, dt, T):
+    got = [one(axis, *d, dt) for d in (few, many)]
+    assert all(p["kernel"] == "bluestein" for p in got) and tuple(p["T"] for p in got) == T
