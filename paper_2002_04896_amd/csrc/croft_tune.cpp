@@ -175,6 +175,15 @@ const BuiltinSized kBuiltinSized[] = {
     {256, 1, 0, 1, kWhole, 128, 0, 0, 1, 0},
     {256, 1, 0, 2, kWhole, 128, 0, 0, 1, 0},
     {256, 1, 1, 1, kWhole, 512, 0, 0, 0, 1},
+    // and the non-temporal z stores stay off grids that the eight 4 MiB L2s hold
+    // between calls (whole transforms, us, non-temporal against plain: complex64
+    // 128 x 72 x 256 (18 MiB) 31.5, 27.7, 128 x 96 x 256 35.4, 28.4, 128 x 120 x 256 40.0,
+    // 34.2, but 128 x 64 x 256 (16 MiB) 25.5, 32.2, 256 x 64 x 256 (32 MiB) 34.5, 36.5;
+    // complex128 128 x 88 x 128 (22 MiB) 49.1, 45.7, 256 x 56 x 128 50.2, 45.3, 128 x 52 x
+    // 256 48.9, 44.1, real 192 x 64 x 256 39.4, 33.8, but 20 and 30 MiB level)
+    {256, 1, 0, 2, kWhole, 0, 16, 31, 1, 0},
+    {128, 1, 1, 2, kWhole, 0, 20, 29, 2, 0},
+    {256, 1, 1, 2, kWhole, 0, 20, 29, 6, 0},
     // complex64 384 beyond the cache: the 32-line wide tile on one wave (whole
     // transforms, us, against the grouped stages: 384^3 496, 516, 384 x 384 x 256
     // 357, 363; in the cache 384 x 384 x 96 124, 123, 64 x 384 x 160 47, 44)
@@ -355,7 +364,10 @@ void wisdom_record(int n, int kind, int dtype, int axis, int cand, int waves, bo
 // before: complex64 75 14.6, 40 (15.5, 42), 150 25, 88 (30, 101), 200 34, 126
 // (38, 138), 256 39, 142 (42, 147), 360 67, 228 (87, 317), 512 95, 299 (118,
 // 373); complex128 108 32, 126 (38, 142), 180 50, 207 (74, 303), 256 97, 270
-// (93, 303), 512 209, 548 (244, 704)).  Above 256 complex64 has 16- and 8-line
+// (93, 303), 512 209, 548 (244, 704)), but complex128 128 on whole-line rows: the
+// wide stage-by-stage tile (whole convolutions 512 x 400 x 128 454, 470, 256 x 400 x
+// 128 228, 235, 512 x 128 x 128 140, 143; on partial ones, 512 x 300 x 128, 333,
+// 320).  Above 256 complex64 has 16- and 8-line
 // tiles: the narrow ones (half a line of memory each, so in XCD order, but
 // more blocks on a CU) where rows share lines anyway and the spectrum stays in
 // the last-level cache (97 x 180 lines: 360 29 against 39, 512 35 against 46;
@@ -365,7 +377,8 @@ void conv_choice(int n, int dtype, long long spectrum_bytes, bool partial_lines,
     const bool narrow = partial_lines && spectrum_bytes <= (64LL << 20);
     *cand = 0;
     *waves = 1;  // the stage-by-stage tiles: one wave of resident blocks
-    if (n == 128 || n == 256 || n == 1024 || (n == 512 && dtype == kC128)) *cand = 2;
+    if (n == 128 && dtype == kC128 && !partial_lines) *cand = 1;
+    else if (n == 128 || n == 256 || n == 1024 || (n == 512 && dtype == kC128)) *cand = 2;
     else if (dtype == kC64 && (n == 384 || n == 512)) *cand = narrow ? 3 : 2;
     else if (dtype == kC64 && n > 256 && n < 512) *cand = narrow ? 1 : 0;
 }

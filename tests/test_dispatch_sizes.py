@@ -46,13 +46,22 @@ def test_complex128_streaming_first_pass(dims, cand):
     ("y", (64, 256, 32), C64, ("1", "0")), ("y", (64, 256, 33), C64, ("2", "0")),
     ("z", (64, 32, 256), C64, ("1", "0")), ("z", (64, 33, 256), C64, ("5", "0")),
     ("y", (64, 256, 64), C128, ("0", "1")), ("y", (64, 256, 65), C128, ("4", "0")),
-    ("y", (384, 384, 384), C64, ("2", "1")), ("z", (384, 384, 384), C64, ("2", "1")),
+    ("z", (128, 64, 256), C64, ("5", "0")), ("z", (128, 72, 256), C64, ("1", "0")), ("z", (256, 62, 256), C64, ("1", "0")),
+    ("z", (128, 128, 256), C64, ("5", "0")), ("z", (128, 80, 128), C128, ("5", "0")), ("z", (128, 88, 128), C128, ("2", "0")),
+    ("z", (256, 58, 128), C128, ("2", "0")), ("z", (256, 60, 128), C128, ("5", "0")), ("z", (128, 44, 256), C128, ("6", "0")),
+    ("z", (128, 128, 128), C128, ("5", "0")), ("y", (384, 384, 384), C64, ("2", "1")), ("z", (384, 384, 384), C64, ("2", "1")),
     ("y", (384, 384, 96), C64, ("8", "0")), ("y", (383, 384, 384), C64, ("8", "0")),
     ("y", (512, 512, 64), C128, ("4", "2")), ("y", (512, 512, 512), C128, ("4", "0")),
     ("y", (512, 512, 32), C128, ("4", "0"))])
 def test_choices_by_size(axis, dims, dt, choice):
     p = one(axis, *dims, dt)
     assert (p["candidate"], p["waves"]) == choice
+
+
+@pytest.mark.parametrize("dims,cand", [((512, 400, 128), "1"), ((512, 300, 128), "2")])
+def test_fused_complex128_128_by_alignment(dims, cand):
+    p = [q for q in parse_describe(croft.croft_plan_describe_convolution(*dims, C128))[1] if q["kind"] == "fused"]
+    assert p[0]["candidate"] == cand
 
 
 # the last launch that takes the stage-by-stage tile and the first that takes
