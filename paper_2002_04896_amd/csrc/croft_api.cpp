@@ -146,6 +146,10 @@ long long pass_bytes(const PassLaunch &p, int dtype) {
     return p.nlines * p.nw * p.n * (long long)element_bytes(dtype);
 }
 
+void set_class(PassLaunch *p, int dtype, bool z_first) {
+    p->measure_class = measure_class(pass_bytes(*p, dtype), strided_kind(p->kind) && partial_lines(*p, dtype), z_first);
+}
+
 // A built-in non-temporal first pass gives way to the plain tile (padded where
 // there is one, candidate 1) where the grid stays in the 256 MB last-level
 // cache, from which the next pass reads it (us, both directions, non-temporal
@@ -203,11 +207,12 @@ int default_waves(const PassLaunch &p, int dtype) {
 // 215, 186, 512 x 512 x 128 168, 154, 256 x 128 x 512 110, 93.6, 512^3 617,
 // 586, 96 x 96 x 1024 68.1, 66.8; complex128 256^3 212, 185, 256 x 256 x 128
 // 107.6, 93.5).
-void pass_choice(const PassLaunch &p, int dtype, int dir, int *cand, int *waves, bool z_first = false) {
+void pass_choice(PassLaunch &p, int dtype, int dir, int *cand, int *waves, bool z_first = false) {
     const int axis = wisdom_axis(p.kind, p.axis);
+    set_class(&p, dtype, z_first && axis == 2);
     *cand = 0;
     *waves = default_waves(p, dtype);
-    if (wisdom_measured(p.n, p.kind, dtype, axis, cand, waves)) return;
+    if (wisdom_measured(p.n, p.kind, dtype, axis, p.measure_class, cand, waves)) return;
     const int builtin_axis = z_first && axis == 2 ? 1 : axis;
     const long long row_lines = (p.es * (long long)element_bytes(dtype) + 127) / 128;
     const PassSize size{pass_bytes(p, dtype), p.kind == kStrided ? row_lines * p.nw : 0,
@@ -354,7 +359,8 @@ int build_unfused_passes(const Geometry &g, int dtype, int dir, int flags, std::
         p.nlines = N / p.n;
         p.nw = 1;
         int cand = 0, waves = default_waves(p, dtype);
-        wisdom_lookup(p.n, kContiguous, dtype, dir, -1, &cand, &waves);
+        set_class(&p, dtype, false);
+        wisdom_lookup(p.n, kContiguous, dtype, dir, -1, p.measure_class, &cand, &waves);
         const bool generic = (flags & CROFT_FORCE_GENERIC) != 0 || p.n == 1;
         if (!select_kernel(p.n, kContiguous, dtype, generic, cand, &p.cfg)) return no_kernel(p.n, dtype);
         if (!lane_offset_fits(p, dtype) && !select_kernel(p.n, kContiguous, dtype, true, 0, &p.cfg))
@@ -393,7 +399,8 @@ int build_real_passes(const Geometry &g, int dtype, int dir, int flags, std::vec
     const bool one_wave = m >= 480 && !(dtype == CROFT_C64 && m == 720 && tune_dir != CROFT_BACKWARD) &&
                           !(dtype == CROFT_C128 && m == 576 && tune_dir == CROFT_BACKWARD);
     int cand = 0, waves = one_wave ? 1 : 0;
-    wisdom_lookup(m, kRealX, dtype, tune_dir, -1, &cand, &waves);
+    set_class(&xp, dtype, false);
+    wisdom_lookup(m, kRealX, dtype, tune_dir, -1, xp.measure_class, &cand, &waves);
     if (!select_kernel(m, kRealX, dtype, false, cand, &xp.cfg))
         return fail(CROFT_ERR_UNSUPPORTED_SIZE, "no real x kernel for nx = %d (half length %d)", g.nx, m);
     xp.cfg.grid_waves = waves;
@@ -442,7 +449,8 @@ int build_conv_passes(const Geometry &g, int dtype, int flags, std::vector<PassL
     c.kind = kConvZ;
     c.hx = (long long)g.nx / 2 + 1;
     int cand = 0, waves = 1;
-    if (!wisdom_lookup(c.n, kConvZ, dtype, 0, -1, &cand, &waves))
+    set_class(&c, dtype, false);
+    if (!wisdom_lookup(c.n, kConvZ, dtype, 0, -1, c.measure_class, &cand, &waves))
         conv_choice(c.n, dtype, c.hx * g.ny * g.nz * (long long)element_bytes(dtype), partial_lines(c, dtype), &cand,
                     &waves);
     const bool compiled = select_kernel(c.n, kConvZ, dtype, false, cand, &c.cfg);
@@ -752,22 +760,24 @@ int measure_passes(croft_plan *p) {
     }
     const bool persist = !(p->flags & CROFT_NO_WISDOM);
     const bool inv = p->dir == CROFT_BACKWARD;
-    // (n, kind, wisdom axis) -> configuration: strided passes are tuned per
-    // axis, as their strides differ
-    std::map<std::tuple<int, int, int>, KernelConfig> best;
+    // (n, kind, wisdom axis, class) -> configuration: strided passes are tuned
+    // per axis, as their strides differ, and every pass per class
+    std::map<std::tuple<int, int, int, int>, KernelConfig> best;
     for (auto &ps : p->passes) {
         for (PassLaunch &pl : ps) {
             const int wax = wisdom_axis(pl.kind, pl.axis);
-            if (pl.cfg.generic || best.count({pl.n, pl.kind, wax})) continue;
+            if (pl.cfg.generic || best.count({pl.n, pl.kind, wax, pl.measure_class})) continue;
             float best_ms = 1e30f;
             KernelConfig pick = pl.cfg;
-            // every pass of the plan with this (length, kind, axis): a choice
-            // is timed on all the geometries it will run (e.g. the z passes of
-            // every grid of a batched plan)
+            // every pass of the plan with this (length, kind, axis, class): a
+            // choice is timed on all the geometries it will run (e.g. the z
+            // passes of every grid of its size in a batched plan)
             std::vector<const PassLaunch *> same;
             for (auto &ps2 : p->passes)
                 for (const PassLaunch &q : ps2)
-                    if (q.n == pl.n && q.kind == pl.kind && wisdom_axis(q.kind, q.axis) == wax) same.push_back(&q);
+                    if (q.n == pl.n && q.kind == pl.kind && wisdom_axis(q.kind, q.axis) == wax &&
+                        q.measure_class == pl.measure_class)
+                        same.push_back(&q);
             for (int c : kernel_candidates(pl.n, pl.kind, p->dtype)) {
                 if (rc != CROFT_SUCCESS) break;
                 KernelConfig cfg;
@@ -830,8 +840,8 @@ int measure_passes(croft_plan *p) {
                 }
             }
             if (rc != CROFT_SUCCESS) break;
-            best[{pl.n, pl.kind, wax}] = pick;
-            wisdom_record(pl.n, pl.kind, p->dtype, wax, pick.candidate, pick.grid_waves, persist);
+            best[{pl.n, pl.kind, wax, pl.measure_class}] = pick;
+            wisdom_record(pl.n, pl.kind, p->dtype, wax, pl.measure_class, pick.candidate, pick.grid_waves, persist);
         }
     }
     cleanup();
@@ -839,7 +849,7 @@ int measure_passes(croft_plan *p) {
     for (auto &ps : p->passes)
         for (PassLaunch &pl : ps) {
             if (pl.cfg.generic) continue;  // a pass the planner sent to the runtime-radix kernel keeps it
-            auto it = best.find({pl.n, pl.kind, wisdom_axis(pl.kind, pl.axis)});
+            auto it = best.find({pl.n, pl.kind, wisdom_axis(pl.kind, pl.axis), pl.measure_class});
             if (it != best.end()) pl.cfg = it->second;
         }
     return CROFT_SUCCESS;
@@ -1050,7 +1060,7 @@ int measure_batch_shapes(croft_plan *p) {
         }
         if (rc != CROFT_SUCCESS) break;
         kv.second = pick;
-        wisdom_record(kv.first.first, kBatchWisdomKind + kv.first.second, p->dtype, -1, pick, 0, persist);
+        wisdom_record(kv.first.first, kBatchWisdomKind + kv.first.second, p->dtype, -1, 0, pick, 0, persist);
     }
     cleanup();
     if (rc != CROFT_SUCCESS) return rc;
@@ -1071,7 +1081,7 @@ int build_batch_tables(croft_plan *p) {
     for (size_t g : p->bgrids)
         for (const PassLaunch &pl : p->passes[g]) {
             int shape = 0, waves = 0;
-            if (!wisdom_lookup(pl.n, kBatchWisdomKind + pl.kind, p->dtype, p->dir, -1, &shape, &waves) || shape < 0 ||
+            if (!wisdom_lookup(pl.n, kBatchWisdomKind + pl.kind, p->dtype, p->dir, -1, 0, &shape, &waves) || shape < 0 ||
                 shape >= batch_shape_count(p->dtype))
                 shape = 0;
             p->bshape[{pl.n, pl.kind}] = shape;

@@ -107,6 +107,7 @@ struct PassLaunch {
     const void *chirp = nullptr;  // Bluestein: exp(-pi i j^2 / n), j < n
     const void *bhat = nullptr;   // Bluestein: DFT of the conjugate chirp kernel, / m
     int dir = 0;               // 0: the plan's direction; else CROFT_FORWARD / CROFT_BACKWARD
+    int measure_class = 0;     // what a measured choice for it is keyed on besides length, kind, dtype and axis
     long long hx = 0;          // kConvZ: spectrum elements per x-line
 };
 
@@ -195,8 +196,9 @@ hipError_t noalloc_scratch(int device, int8_t **ptr);
 // dir: -1 forward, +1 backward, 0 a pass that runs in both directions (the
 // forward-only built-in choices apply to -1 only).  axis: the grid axis of a
 // strided pass (a choice for that axis first, then one for any axis), -1
-// for the other kinds.
-bool wisdom_lookup(int n, int kind, int dtype, int dir, int axis, int *cand, int *waves);
+// for the other kinds.  cls: the pass's measure class, 0 where there is none
+// (the batched kernel's shapes).
+bool wisdom_lookup(int n, int kind, int dtype, int dir, int axis, int cls, int *cand, int *waves);
 // Its built-in part alone.
 bool builtin_choice(int n, int kind, int dtype, int dir, int axis, int *cand, int *waves);
 // What a built-in choice for a size goes by: the bytes a pass reads and, strided,
@@ -210,11 +212,20 @@ struct PassSize {
 bool sized_choice(int n, int kind, int dtype, int axis, const PassSize &size, int *cand, int *waves);
 // The part of it that was measured for this process or its CROFT_WISDOM file
 // (no built-in choice).
-bool wisdom_measured(int n, int kind, int dtype, int axis, int *cand, int *waves);
+bool wisdom_measured(int n, int kind, int dtype, int axis, int cls, int *cand, int *waves);
+// The class of passes a measured choice holds for, 1 or more: those that the
+// built-in choices above treat alike.  The passes read as many bytes to a
+// factor of two (up to 1, 2, 4, .. MiB), their rows end inside 128-byte lines or
+// not, and they are a z pass that others follow or not.
+inline int measure_class(long long bytes, bool partial_lines, bool z_first) {
+    int step = 0;
+    while (step < 20 && (1LL << (20 + step)) < bytes) ++step;
+    return 1 + (partial_lines ? 1 : 0) + (z_first ? 2 : 0) + 4 * step;
+}
 // The choice for a fused multiply pass that wisdom_lookup has none for.
 // partial_lines: its rows are not whole 128-byte lines.
 void conv_choice(int n, int dtype, long long spectrum_bytes, bool partial_lines, int *cand, int *waves);
-void wisdom_record(int n, int kind, int dtype, int axis, int cand, int waves, bool persist);
+void wisdom_record(int n, int kind, int dtype, int axis, int cls, int cand, int waves, bool persist);
 // Slab count K of the pipelined schedule for a grid and dtype (K divides nz).
 bool slab_wisdom_lookup(int nx, int ny, int nz, int dtype, int *k);
 void slab_wisdom_record(int nx, int ny, int nz, int dtype, int k, bool persist);

@@ -7,6 +7,11 @@
 // names a file, plans also read it and CROFT_MEASURE plans append to it.
 // File format, one choice per line:  n kind dtype candidate waves [axis]
 // (and "slabs nx ny nz dtype K" for the slab count of a grid, below)
+// A choice that CROFT_MEASURE made holds for the class of passes it was timed
+// on (measure_class: size to a factor of two, alignment of the rows, place in
+// the plan), as the best configuration changes between them; its line has
+// dtype + 4 class in the place of dtype.  A line with a plain dtype serves
+// every class.
 // A strided pass also has a choice of its own per grid axis (1 = y, 2 = z:
 // their strides differ, and so can their best tiles); a line without an axis
 // serves every axis.  Lookup order: the CROFT_WISDOM file, choices measured
@@ -16,7 +21,7 @@
 // some sizes only; kinds 2 and 3, the real x pass and the
 // fused multiply pass, on real and convolution plans of cubic grids), then
 // candidate 0 on the grid size the caller starts from.  At each step an entry for the pass's
-// axis comes before one for any axis.
+// axis comes before one for any axis, and one for its class before one for any.
 #include <cstdio>
 #include <cstdlib>
 #include <map>
@@ -258,10 +263,11 @@ const BuiltinSized kBuiltinSized[] = {
 };
 
 std::mutex g_mu;
-std::map<std::tuple<int, int, int, int>, std::pair<int, int>> g_mem;  // (n, kind, dtype, axis or -1)
+std::map<std::tuple<int, int, int, int, int>, std::pair<int, int>> g_mem;  // (n, kind, dtype, class, axis or -1)
 
-// The last matching line for this axis (axis >= 0) or for any axis (axis -1).
-bool read_file(const char *path, int n, int kind, int dtype, int axis, int *cand, int *waves) {
+// The last matching line for this axis (axis >= 0) or for any axis (axis -1),
+// and for this class or (0) for any.
+bool read_file(const char *path, int n, int kind, int dtype, int cls, int axis, int *cand, int *waves) {
     FILE *f = std::fopen(path, "r");
     if (!f) return false;
     bool found = false;
@@ -269,7 +275,7 @@ bool read_file(const char *path, int n, int kind, int dtype, int axis, int *cand
     char line[256];
     while (std::fgets(line, sizeof line, f)) {
         const int got = std::sscanf(line, "%d %d %d %d %d %d", &a, &b, &c, &d, &e, &x);
-        if (got < 5 || a != n || b != kind || c != dtype) continue;
+        if (got < 5 || a != n || b != kind || c != dtype + 4 * cls) continue;
         if ((axis < 0 && got == 5) || (axis >= 0 && got == 6 && x == axis)) {
             *cand = d;
             *waves = e;
@@ -281,16 +287,16 @@ bool read_file(const char *path, int n, int kind, int dtype, int axis, int *cand
 }
 }  // namespace
 
-bool wisdom_measured(int n, int kind, int dtype, int axis, int *cand, int *waves) {
+bool wisdom_measured(int n, int kind, int dtype, int axis, int cls, int *cand, int *waves) {
     std::lock_guard<std::mutex> lk(g_mu);
+    const int axes[2] = {axis, -1}, classes[2] = {cls, 0};
     const char *path = std::getenv("CROFT_WISDOM");
-    if (path && *path) {
-        if (axis >= 0 && read_file(path, n, kind, dtype, axis, cand, waves)) return true;
-        if (read_file(path, n, kind, dtype, -1, cand, waves)) return true;
-    }
-    const int axes[2] = {axis, -1};
+    if (path && *path)
+        for (int i = axis >= 0 ? 0 : 1; i < 2; ++i)
+            for (int j = cls > 0 ? 0 : 1; j < 2; ++j)
+                if (read_file(path, n, kind, dtype, classes[j], axes[i], cand, waves)) return true;
     for (int i = axis >= 0 ? 0 : 1; i < 2; ++i) {
-        auto it = g_mem.find({n, kind, dtype, axes[i]});
+        auto it = g_mem.find({n, kind, dtype, cls, axes[i]});
         if (it != g_mem.end()) {
             *cand = it->second.first;
             *waves = it->second.second;
@@ -300,8 +306,8 @@ bool wisdom_measured(int n, int kind, int dtype, int axis, int *cand, int *waves
     return false;
 }
 
-bool wisdom_lookup(int n, int kind, int dtype, int dir, int axis, int *cand, int *waves) {
-    return wisdom_measured(n, kind, dtype, axis, cand, waves) ||
+bool wisdom_lookup(int n, int kind, int dtype, int dir, int axis, int cls, int *cand, int *waves) {
+    return wisdom_measured(n, kind, dtype, axis, cls, cand, waves) ||
            builtin_choice(n, kind, dtype, dir, axis, cand, waves);
 }
 
@@ -347,14 +353,15 @@ bool builtin_choice(int n, int kind, int dtype, int dir, int axis, int *cand, in
     return false;
 }
 
-void wisdom_record(int n, int kind, int dtype, int axis, int cand, int waves, bool persist) {
+void wisdom_record(int n, int kind, int dtype, int axis, int cls, int cand, int waves, bool persist) {
     std::lock_guard<std::mutex> lk(g_mu);
-    g_mem[{n, kind, dtype, axis}] = {cand, waves};
+    g_mem[{n, kind, dtype, cls, axis}] = {cand, waves};
     const char *path = std::getenv("CROFT_WISDOM");
     if (!persist || !path || !*path) return;
     if (FILE *f = std::fopen(path, "a")) {
-        if (axis >= 0) std::fprintf(f, "%d %d %d %d %d %d\n", n, kind, dtype, cand, waves, axis);
-        else std::fprintf(f, "%d %d %d %d %d\n", n, kind, dtype, cand, waves);
+        const int key = dtype + 4 * cls;
+        if (axis >= 0) std::fprintf(f, "%d %d %d %d %d %d\n", n, kind, key, cand, waves, axis);
+        else std::fprintf(f, "%d %d %d %d %d\n", n, kind, key, cand, waves);
         std::fclose(f);
     }
 }
