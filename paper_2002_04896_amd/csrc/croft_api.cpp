@@ -796,7 +796,9 @@ int measure_passes(croft_plan *p) {
                 if ((rc = prepare_kernel(&cfg)) != CROFT_SUCCESS) break;
                 // a choice serves both directions (the wisdom key has none), and
                 // the two instantiations of a configuration can differ in speed
-                // (e.g. one spills registers), so both are timed
+                // (e.g. one spills registers), so both are timed; a candidate
+                // that runs both in one kernel (the grouped stages) is timed
+                // once, and the mean over the directions compared
                 const int ndir = cfg.func_inv != cfg.func ? 2 : 1;
                 for (int waves : {1, 2, 4, 0}) {
                     if (cfg.one_tile && waves != 0) continue;
@@ -823,7 +825,7 @@ int measure_passes(croft_plan *p) {
                                 if (e == hipSuccess) e = hipEventElapsedTime(&ms, t0, t1);
                                 best_rep = std::min(best_rep, ms);
                             }
-                            total += best_rep;
+                            total += best_rep / (float)ndir;
                         }
                         if (e != hipSuccess) break;
                     }
