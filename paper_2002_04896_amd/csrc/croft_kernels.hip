@@ -260,18 +260,17 @@ __global__ void __launch_bounds__(256) fft_generic_conv(const PassArgs a) {
     if (tid == 0) a.partial[blockIdx.x] = sum[0];
 }
 
-const std::vector<Entry> &table() {
-    static const std::vector<Entry> t = [] {
-        std::vector<Entry> v;
+// The compiled configurations of a length, 1 .. kMaxLength.
+const std::vector<Entry> &entries_of(int n) {
+    static const std::vector<std::vector<Entry>> t = [] {
+        std::vector<std::vector<Entry>> v(kMaxLength + 1);
         for (auto f : {entries_c64, entries_c128, entries_c16f, entries_c16b, group_entries_c64, group_entries_c128,
                        group_entries_c16f, group_entries_c16b, group_entries_c16f_x, group_entries_c16b_x,
-                       group_conv_entries_c64, group_conv_entries_c128}) {
-            std::vector<Entry> e = f();
-            v.insert(v.end(), e.begin(), e.end());
-        }
+                       group_conv_entries_c64, group_conv_entries_c128})
+            for (const Entry &e : f()) v[e.n].push_back(e);
         return v;
     }();
-    return t;
+    return t[n];
 }
 
 template <bool TWL>
@@ -327,15 +326,15 @@ __global__ void __launch_bounds__(1024) sum_partials(const double *partial, int 
 }  // namespace
 
 int grouped_candidate(int n, int dtype) {
-    for (const Entry &e : table())
-        if (e.n == n && e.kind == kStrided && e.dtype == dtype && e.one_tile) return e.cand;
+    for (const Entry &e : entries_of(n))
+        if (e.kind == kStrided && e.dtype == dtype && e.one_tile) return e.cand;
     return -1;
 }
 
 std::vector<int> kernel_candidates(int n, int kind, int dtype) {
     std::vector<int> c;
-    for (const Entry &e : table())
-        if (e.n == n && e.kind == kind && e.dtype == dtype) c.push_back(e.cand);
+    for (const Entry &e : entries_of(n))
+        if (e.kind == kind && e.dtype == dtype) c.push_back(e.cand);
     std::sort(c.begin(), c.end());
     return c;
 }
@@ -344,8 +343,8 @@ bool select_kernel(int n, int kind, int dtype, bool force_generic, int cand, Ker
     if (n < 1 || n > kMaxLength) return false;
     if (!force_generic || kind == kRealX || kind == kConvZ) {
         const Entry *pick = nullptr;
-        for (const Entry &e : table()) {
-            if (e.n == n && e.kind == kind && e.dtype == dtype) {
+        for (const Entry &e : entries_of(n)) {
+            if (e.kind == kind && e.dtype == dtype) {
                 if (e.cand == 0 && !pick) pick = &e;
                 if (e.cand == cand) pick = &e;
             }
