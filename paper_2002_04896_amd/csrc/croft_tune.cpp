@@ -217,7 +217,7 @@ const BuiltinSized kBuiltinSized[] = {
     {480, 1, 1, -1, kAny, 256, 0, 0, 1, 0}, {576, 1, 1, -1, kAny, 128, 0, 0, 1, 0},
     {640, 1, 1, -1, kAny, 128, 0, 0, 1, 0}, {768, 1, 1, -1, kAny, 512, 0, 0, 1, 0},
     {960, 1, 1, -1, kAny, 128, 0, 0, 1, 0},
-    {32, 1, kHalves, -1, kWhole, 8192, 0, 0, 1, 0}, {60, 1, kHalves, -1, kWhole, 1024, 0, 0, 1, 0},
+    {32, 1, kHalves, -1, kWhole, 2048, 0, 0, 1, 0}, {60, 1, kHalves, -1, kWhole, 1024, 0, 0, 1, 0},
     {60, 1, kHalves, -1, kPartial, 256, 0, 0, 1, 0}, {64, 1, kHalves, -1, kWhole, 4096, 0, 0, 1, 0},
     {64, 1, kHalves, -1, kPartial, 256, 0, 0, 1, 0}, {80, 1, kHalves, -1, kWhole, 512, 0, 0, 1, 0},
     {80, 1, kHalves, -1, kPartial, 128, 0, 0, 1, 0}, {96, 1, kHalves, -1, kWhole, 512, 0, 0, 1, 0},
@@ -371,10 +371,10 @@ void wisdom_record(int n, int kind, int dtype, int axis, int cls, int cand, int 
 // before: complex64 75 14.6, 40 (15.5, 42), 150 25, 88 (30, 101), 200 34, 126
 // (38, 138), 256 39, 142 (42, 147), 360 67, 228 (87, 317), 512 95, 299 (118,
 // 373); complex128 108 32, 126 (38, 142), 180 50, 207 (74, 303), 256 97, 270
-// (93, 303), 512 209, 548 (244, 704)), but complex128 128 on whole-line rows: the
-// wide stage-by-stage tile (whole convolutions 512 x 400 x 128 454, 470, 256 x 400 x
-// 128 228, 235, 512 x 128 x 128 140, 143; on partial ones, 512 x 300 x 128, 333,
-// 320).  Above 256 complex64 has 16- and 8-line
+// (93, 303), 512 209, 548 (244, 704)), but complex128 128 on whole-line rows beyond
+// 64 MiB: the wide stage-by-stage tile (whole convolutions 512 x 400 x 128 454, 470,
+// 256 x 400 x 128 228, 235, 512 x 128 x 128 140, 143; 128^3 (17 MB) 63.8, 61.1; on
+// partial ones, 512 x 300 x 128, 333, 320).  Above 256 complex64 has 16- and 8-line
 // tiles: the narrow ones (half a line of memory each, so in XCD order, but
 // more blocks on a CU) where rows share lines anyway and the spectrum stays in
 // the last-level cache (97 x 180 lines: 360 29 against 39, 512 35 against 46;
@@ -384,7 +384,7 @@ void conv_choice(int n, int dtype, long long spectrum_bytes, bool partial_lines,
     const bool narrow = partial_lines && spectrum_bytes <= (64LL << 20);
     *cand = 0;
     *waves = 1;  // the stage-by-stage tiles: one wave of resident blocks
-    if (n == 128 && dtype == kC128 && !partial_lines) *cand = 1;
+    if (n == 128 && dtype == kC128 && !partial_lines && spectrum_bytes > (64LL << 20)) *cand = 1;
     else if (n == 128 || n == 256 || n == 1024 || (n == 512 && dtype == kC128)) *cand = 2;
     else if (dtype == kC64 && (n == 384 || n == 512)) *cand = narrow ? 3 : 2;
     else if (dtype == kC64 && n > 256 && n < 512) *cand = narrow ? 1 : 0;

@@ -58,7 +58,7 @@ def test_choices_by_size(axis, dims, dt, choice):
     assert (p["candidate"], p["waves"]) == choice
 
 
-@pytest.mark.parametrize("dims,cand", [((512, 400, 128), "1"), ((512, 300, 128), "2")])
+@pytest.mark.parametrize("dims,cand", [((512, 400, 128), "1"), ((512, 300, 128), "2"), ((128, 128, 128), "2")])
 def test_fused_complex128_128_by_alignment(dims, cand):
     p = [q for q in parse_describe(croft.croft_plan_describe_convolution(*dims, C128))[1] if q["kind"] == "fused"]
     assert p[0]["candidate"] == cand
