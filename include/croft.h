@@ -92,7 +92,7 @@ enum croft_flags {
     CROFT_ESTIMATE = 0,       /* default heuristics, no device timing at create */
     CROFT_MEASURE = 1,        /* time candidate configurations at create (autotune) */
     CROFT_FORCE_GENERIC = 2,  /* use the runtime-radix kernels for every pass */
-    CROFT_NO_WISDOM = 4,      /* MEASURE: neither read nor write the wisdom file */
+    CROFT_NO_WISDOM = 4,      /* MEASURE: record the choices in this process only, not in the wisdom file */
     CROFT_UNFUSED = 16,       /* croft_plan_create_ex, C64/C128: the paper's Option 2 (Section 5.1,
                                  no overlap), kept as the measured baseline of the fused passes:
                                  the three FFTs run on contiguous lines with three standalone

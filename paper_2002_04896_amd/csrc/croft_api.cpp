@@ -215,7 +215,7 @@ void pass_choice(PassLaunch &p, int dtype, int dir, int *cand, int *waves, bool 
     if (wisdom_measured(p.n, p.kind, dtype, axis, p.measure_class, cand, waves)) return;
     const int builtin_axis = z_first && axis == 2 ? 1 : axis;
     const long long row_lines = (p.es * (long long)element_bytes(dtype) + 127) / 128;
-    const PassSize size{pass_bytes(p, dtype), p.kind == kStrided ? row_lines * p.nw : 0,
+    const PassSize size{pass_bytes(p, dtype), p.kind == kStrided ? row_lines * p.nw : 0, p.nw,
                         p.kind == kStrided && partial_lines(p, dtype)};
     if (sized_choice(p.n, p.kind, dtype, builtin_axis, size, cand, waves)) return;
     if (p.kind == kStrided && !is_half(dtype) && partial_lines(p, dtype)) {

@@ -833,8 +833,8 @@ __device__ __forceinline__ int tw_source(int i) {
 // store() writes them to LDS, after; the tile's loads are then in flight while
 // the table arrives, instead of waiting for it and a barrier.  A barrier must
 // follow store().  (Longer tables are copied by store() alone.)  Used by the
-// batched tiles, which run once per block: 64 mixed complex64 grids 336 -> 331
-// us.  In fft_static and the real x pass the registers it holds cost more than
+// batched tiles, which run once per block: 64 mixed complex64 grids 334 -> 331
+// us, about what two runs differ by.  In fft_static and the real x pass the registers it holds cost more than
 // it hides (complex128 128^3 31 -> 34 us, real 160 x 144 x 150 43 -> 46).
 template <int COUNT, int BLOCK, typename R>
 struct TableCopy {

@@ -202,10 +202,10 @@ bool wisdom_lookup(int n, int kind, int dtype, int dir, int axis, int cls, int *
 // Its built-in part alone.
 bool builtin_choice(int n, int kind, int dtype, int dir, int axis, int *cand, int *waves);
 // What a built-in choice for a size goes by: the bytes a pass reads and, strided,
-// its 128-byte row segments (a tile is one to two of them wide) and whether
-// rows end inside a 128-byte line.
+// its 128-byte row segments (a tile is one to two of them wide), its planes (nw)
+// and whether rows end inside a 128-byte line.
 struct PassSize {
-    long long bytes = 0, segments = 0;
+    long long bytes = 0, segments = 0, planes = 1;
     bool partial_lines = false;
 };
 // The built-in choices that hold for some sizes only; before builtin_choice.

@@ -57,7 +57,6 @@ const Builtin kBuiltin[] = {
     {960, 0, 0, 3, 0},
     {512, 0, 0, 3, 0}, {512, 1, 0, 4, 4}, {1024, 0, 0, 3, 0}, {1024, 1, 0, 7, 1}, {32, 2, 0, 0, 0},
     {64, 2, 0, 0, 2}, {64, 3, 0, 0, 2}, {128, 2, 0, 0, 1}, {256, 2, 0, 1, 0},
-    
     // complex64 batched tile shapes (kinds 4 and 5: the batched kernel's
     // contiguous and strided passes; candidate = shape), the majority of six
     // CROFT_MEASURE runs (both directions) on the 64-grid PME batch; the
@@ -75,7 +74,6 @@ const Builtin kBuiltin[] = {
     {480, 0, 1, 3, 0}, {576, 0, 1, 3, 0}, {640, 0, 1, 3, 0}, {768, 0, 1, 3, 0},
     {512, 0, 1, 3, 0}, {512, 1, 1, 4, 2}, {1024, 0, 1, 2, 0}, {1024, 1, 1, 5, 0}, {32, 2, 1, 0, 2},
     {64, 2, 1, 0, 1}, {64, 3, 1, 0, 0}, {128, 2, 1, 0, 1}, {256, 2, 1, 0, 2},
-    
     // FP16 storage (strided 128 and 256: the grouped stages; 512 x: the
     // non-temporal contiguous tile on four waves of resident blocks, 0.217 ->
     // 0.195 ms in both directions; the same for BF16)
@@ -116,8 +114,8 @@ const BuiltinAxis kBuiltinAxis[] = {
     // costs in the passes before it, whose output the next one reads: complex64
     // 256^3 z 133 -> 125, 512 x 512 x 256 z 613 -> 541, 512 x 256 x 512 y 570
     // -> 559, 256 x 128 x 256 y 75.3 -> 69.3; complex128 128^3 y 39.5 -> 35.3,
-    // 256^3 y 296 -> 259 (512 x 256 x 512 1166 -> 1180, 256 x 256 x 1024 1283
-    // -> 1243)
+    // 256^3 y 296 -> 259 (512 x 256 x 512 1130 -> 1147, 256 x 256 x 1024 1282
+    // -> 1237)
     {128, 1, 0, 1, 1, 1},
     {128, 1, 0, 2, 5, 0},
     {256, 1, 0, 1, 2, 0},
@@ -162,14 +160,14 @@ const BuiltinAxis kBuiltinAxis[] = {
 };
 
 // Choices for some sizes only, looked up before the tables above: the first
-// entry whose limits hold.  axis -1: any; rows 0: any, 1: whole 128-byte
-// lines, 2: not; segments: at most so many 128-byte row segments (0: no
+// entry whose limits hold.  axis -1: any; rows: any, whole 128-byte lines, not,
+// or whole in a number of planes that is no power of two; segments: at most so many 128-byte row segments (0: no
 // limit); MiB the pass reads: more than `above`, at most `upto` (0: no limit).
 // dtype kHalves: either 16-bit storage.
 struct BuiltinSized {
     int n, kind, dtype, axis, rows, segments, above, upto, cand, waves;
 };
-constexpr int kAny = 0, kWhole = 1, kPartial = 2;
+constexpr int kAny = 0, kWhole = 1, kPartial = 2, kWholeUneven = 3;
 constexpr int kHalves = -1;
 const BuiltinSized kBuiltinSized[] = {
     // 256: the wide tiles of the choices by axis leave most CUs without one on
@@ -180,6 +178,11 @@ const BuiltinSized kBuiltinSized[] = {
     {256, 1, 0, 1, kWhole, 128, 0, 0, 1, 0},
     {256, 1, 0, 2, kWhole, 128, 0, 0, 1, 0},
     {256, 1, 1, 1, kWhole, 512, 0, 0, 0, 1},
+    // and beyond the cache complex128 y keeps the non-temporal one where the planes
+    // are no power of two (512 x 256 x 300 736, 746, 512 x 256 x 400 963, 979, 360 x 256
+    // x 300 506, 520; 512 x 256 x 256 563, 545, 256 x 256 x 1024 1282, 1237, but 512 x
+    // 256 x 512 1130, 1147)
+    {256, 1, 1, 1, kWholeUneven, 0, 256, 0, 5, 0},
     // and the non-temporal z stores stay off grids that the eight 4 MiB L2s hold
     // between calls (whole transforms, us, non-temporal against plain: complex64
     // 128 x 72 x 256 (18 MiB) 31.5, 27.7, 128 x 96 x 256 35.4, 28.4, 128 x 120 x 256 40.0,
@@ -314,7 +317,8 @@ bool wisdom_lookup(int n, int kind, int dtype, int dir, int axis, int cls, int *
 bool sized_choice(int n, int kind, int dtype, int axis, const PassSize &size, int *cand, int *waves) {
     for (const BuiltinSized &b : kBuiltinSized) {
         if (b.n != n || b.kind != kind || (b.dtype == kHalves ? dtype < kC16F : b.dtype != dtype) || (b.axis >= 0 && b.axis != axis)) continue;
-        if (b.rows != kAny && (b.rows == kWhole) == size.partial_lines) continue;
+        if (b.rows != kAny && (b.rows == kPartial) != size.partial_lines) continue;
+        if (b.rows == kWholeUneven && (size.planes & (size.planes - 1)) == 0) continue;
         if (b.segments && size.segments > b.segments) continue;
         if (size.bytes <= ((long long)b.above << 20) || (b.upto && size.bytes > ((long long)b.upto << 20))) continue;
         *cand = b.cand;

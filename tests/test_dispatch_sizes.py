@@ -49,7 +49,8 @@ def test_complex128_streaming_first_pass(dims, cand):
     ("z", (128, 64, 256), C64, ("5", "0")), ("z", (128, 72, 256), C64, ("1", "0")), ("z", (256, 62, 256), C64, ("1", "0")),
     ("z", (128, 128, 256), C64, ("5", "0")), ("z", (128, 80, 128), C128, ("5", "0")), ("z", (128, 88, 128), C128, ("2", "0")),
     ("z", (256, 58, 128), C128, ("2", "0")), ("z", (256, 60, 128), C128, ("5", "0")), ("z", (128, 44, 256), C128, ("6", "0")),
-    ("z", (128, 128, 128), C128, ("5", "0")), ("y", (384, 384, 384), C64, ("2", "1")), ("z", (384, 384, 384), C64, ("2", "1")),
+    ("z", (128, 128, 128), C128, ("5", "0")), ("y", (512, 256, 300), C128, ("5", "0")), ("y", (512, 256, 100), C128, ("4", "0")),
+    ("y", (512, 256, 256), C128, ("4", "0")), ("y", (384, 384, 384), C64, ("2", "1")), ("z", (384, 384, 384), C64, ("2", "1")),
     ("y", (384, 384, 96), C64, ("8", "0")), ("y", (383, 384, 384), C64, ("8", "0")),
     ("y", (512, 512, 64), C128, ("4", "2")), ("y", (512, 512, 512), C128, ("4", "0")),
     ("y", (512, 512, 32), C128, ("4", "0"))])
