@@ -832,14 +832,16 @@ __device__ __forceinline__ int tw_source(int i) {
 // global loads into registers, before the block's first tile is loaded, and
 // store() writes them to LDS, after; the tile's loads are then in flight while
 // the table arrives, instead of waiting for it and a barrier.  A barrier must
-// follow store().  (Longer tables are copied by store() alone.)  Used by the
+// follow store().  (Longer tables and FP64 ones, whose registers cost more, are
+// copied by store() alone, before the tile is loaded.)  Used by the
 // batched tiles, which run once per block: 64 mixed complex64 grids 334 -> 331
-// us, about what two runs differ by.  In fft_static and the real x pass the registers it holds cost more than
+// us, about what two runs differ by; complex128, in two halves, 16 grids 197 ->
+// 203.  In fft_static and the real x pass the registers it holds cost more than
 // it hides (complex128 128^3 31 -> 34 us, real 160 x 144 x 150 43 -> 46).
 template <int COUNT, int BLOCK, typename R>
 struct TableCopy {
     static constexpr int kIter = (COUNT + BLOCK - 1) / BLOCK;
-    static constexpr bool kEarly = kIter <= 4;
+    static constexpr bool kEarly = kIter <= 4 && sizeof(R) == 4;
     cx<R> v[kEarly && kIter > 0 ? kIter : 1];
     template <class Src>
     __device__ __forceinline__ void fetch(const cx<R> *W, int tid, Src src) {
@@ -1676,8 +1678,13 @@ __device__ __forceinline__ void batch_tile(const PassArgs &a, long long tile, un
                   : (L % 64 == 0 ? (int)__builtin_amdgcn_readfirstlane((unsigned)(tid / L)) : tid / L);
     const cx<R> *W = reinterpret_cast<const cx<R> *>(a.tw);
     auto src = [](int i) { return tw_source<Cfg>(i); };
-    TableCopy<Cfg::kTwN, Cfg::kBlock, R> table;
+    using Table = TableCopy<Cfg::kTwN, Cfg::kBlock, R>;
+    Table table;
     table.fetch(W, tid, src);
+    if constexpr (Cfg::kTwN > 0 && !Table::kEarly) {
+        table.store(tws, W, tid, src);
+        __syncthreads();
+    }
     const long long es = KIND == kContiguous ? 1 : a.es;
     const long long tx = KIND == kContiguous ? tile : tile % a.ntiles;
     const long long w = KIND == kContiguous ? 0 : tile / a.ntiles;
@@ -1685,7 +1692,7 @@ __device__ __forceinline__ void batch_tile(const PassArgs &a, long long tile, un
     const unsigned lane = lane_offset<Cfg, St, KIND>(l, t, es);
     Tile<Cfg, St> cur;
     fetch_tile<Cfg, St, KIND, INV>(a, c, t, lane, es, cur);
-    if constexpr (Cfg::kTwN > 0) {
+    if constexpr (Cfg::kTwN > 0 && Table::kEarly) {
         table.store(tws, W, tid, src);
         __syncthreads();
     }
